@@ -119,6 +119,13 @@ struct TagBuf {
   __device__ __forceinline__ u32x4 load2_at(uint32_t off) const {
     return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kScopeDevice);
   }
+  // A pair's first load, before any poll of it: through the caches (a line
+  // cached earlier shows an old tag, never a torn or wrong value, and the polls
+  // that follow are device-scope).  Workgroups of one XCD that read the same
+  // rows then share the fetch in its L2.
+  __device__ __forceinline__ u32x4 first2_at(uint32_t off) const {
+    return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+  }
   __device__ __forceinline__ u32x2 load1_at(uint32_t off) const {
     return __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, kScopeDevice);
   }

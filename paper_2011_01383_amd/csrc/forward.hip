@@ -25,6 +25,7 @@
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
+#include <utility>
 
 #include "cortex_device.hpp"
 #include "cortex_host.hpp"
@@ -36,6 +37,7 @@ constexpr int kFwdThreads = 512;
 constexpr int kFwdWaves = kFwdThreads / 64;
 constexpr int kTileM = 16;
 constexpr int CELL_DAG = 16;                 // internal id of the DAG-RNN cell
+constexpr size_t kStructCacheBudget = 40 * 1024;    // bytes of LDS for the cached linearization
 
 // Optional timeline (builds with -DCORTEX_TRACE only): every workgroup (up to
 // kTraceBlocks) stamps the 100 MHz wall clock at phase boundaries of every
@@ -1099,6 +1101,12 @@ __global__ void __launch_bounds__(kFwdThreads) slice_forward_kernel(FwdArgs a) {
   if (a.retire) retire_tag(a.sync, tag, a.status, a.timeout);
 }
 
+}  // namespace cortex
+
+#include "forward_split.hpp"
+
+namespace cortex {
+
 // ---------------------------------------------------------------------------
 // TreeRNN at H = 64 in one workgroup with every state in LDS.
 //   h = tanh(W [h(slot 0); h(slot 1)] + b),  leaf h = its input row.
@@ -1249,34 +1257,6 @@ constexpr int kDagStepHead = 6;
 constexpr int kDagStepInts = kDagStepHead + kDagStepRows * 3;
 constexpr int kDagStepCap = 60;                    // steps per workgroup list (dynamic LDS)
 constexpr size_t kDagListBytes = (size_t)kDagStepCap * kDagStepInts * sizeof(int);
-
-// Exclusive prefix sum of one value per thread over the workgroup; wsum
-// holds kFwdWaves + 1 ints of LDS.  Returns the exclusive sum, *total the sum.
-__device__ __forceinline__ int block_excl_scan(int v, int *wsum, int *total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o);
-    if (lane >= o) x += y;
-  }
-  if (lane == 63) wsum[wave] = x;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int w = 0; w < kFwdWaves; ++w) {
-      const int t = wsum[w];
-      wsum[w] = run;
-      run += t;
-    }
-    wsum[kFwdWaves] = run;
-  }
-  __syncthreads();
-  const int ex = wsum[wave] + x - v;
-  *total = wsum[kFwdWaves];
-  __syncthreads();
-  return ex;
-}
 
 // Tiles of group `group` at a level of ntile tiles; returns their count.
 // Normally the tiles u = uf, uf + Q, ... with uf = (group - l) mod Q, whole
@@ -3250,8 +3230,6 @@ struct Instance {
   int ablate_bits = 0;             // FwdArgs.ablate bits the kernel honours
 };
 
-constexpr size_t kStructCacheBudget = 40 * 1024;    // bytes of LDS for the cached linearization
-
 // ints of the structure cache: offsets (<= N+1), child rows, input rows, node ids
 // (child-sum: offsets, child rows, input rows; the slice kernels: offsets,
 // source codes, input rows of the leaf-input cells)
@@ -3262,7 +3240,8 @@ static size_t cache_ints(int cell, int32_t N, int32_t K) {
   return (size_t)N + 1 + (size_t)N * segs + (cell == CELL_DAG ? 0 : N);
 }
 
-template <int CELL, int H, int J>
+// kUncached: whether batches beyond the structure cache reach the kernel.
+template <int CELL, int H, int J, bool kUncached = true>
 static void pick_slice(bool cached, Instance &out) {
   out.J = J;
   out.threads = kFwdThreads;
@@ -3270,16 +3249,62 @@ static void pick_slice(bool cached, Instance &out) {
   if constexpr (CELL == CORTEX_CHILDSUM_TREELSTM) {
     out.fn = cached ? childsum_forward_kernel<H, true> : childsum_forward_kernel<H, false>;
   } else {
-    if (knob(CORTEX_KNOB_ABLATE) & 1)       // the instance without model persistence
-      out.fn = cached ? slice_forward_kernel<CELL, H, J, true, true> : slice_forward_kernel<CELL, H, J, false, true>;
+    const bool from_memory = knob(CORTEX_KNOB_ABLATE) & 1;      // the instance without model persistence
+    if (kUncached && !cached)
+      out.fn = from_memory ? slice_forward_kernel<CELL, H, J, !kUncached, true> : slice_forward_kernel<CELL, H, J, !kUncached>;
     else
-      out.fn = cached ? slice_forward_kernel<CELL, H, J, true> : slice_forward_kernel<CELL, H, J, false>;
+      out.fn = from_memory ? slice_forward_kernel<CELL, H, J, true, true> : slice_forward_kernel<CELL, H, J, true>;
     out.ablate_bits = SrcCfg<CELL>::kLeafX ? 3 : 1;
   }
 }
 
+template <int CELL, int H, int J>
+static bool pick_split(Instance &out, int32_t N, bool fused = false) {
+  using D = SplitDims<CELL, H, J>;
+  out.J = J;
+  out.threads = kFwdThreads;
+  out.level_barrier_ok = out.level_range_ok = true;
+  out.ablate_bits = SrcCfg<CELL>::kLeafX ? 3 : 1;
+  if (D::kDag && fused) {
+    out.fn = slice_split_kernel<CELL, H, J, D::kDag>;
+    out.lds = split_list_bytes<D::CODES>(kSplitFusedCap) + (N + small_lin_ints<kFwdThreads>(N, 2)) * sizeof(int);
+  } else {
+    out.fn = (knob(CORTEX_KNOB_ABLATE) & 1) ? slice_split_kernel<CELL, H, J, false, true> : slice_split_kernel<CELL, H, J, false>;
+    out.lds = split_list_bytes<D::CODES>(kSplitCap);
+  }
+  return true;
+}
+
+// The split kernels of the slice cells at H = 256 and 512; false where there
+// is none, or where the fp32 slice kernel is the faster one.  units: the
+// slice-width knob (0 = by the batch size).  us per step (fp32 kernel / this
+// one):
+//   N-ary TreeLSTM 256   1,225 nodes 73.8 / 73.1, 1,568 85.6 / 78.7, 1,960
+//                        98 / 86, 9,800 324 / 166; 490 (one launch) 54 / 60.
+//                        J = 8: at J = 16 the weight and operand registers spill
+//                        (9,800 nodes: 182)
+//   TreeRNN 256          2,550 52.4 / 52.5 (J = 16); 4,900 101 / 91 (64: 95),
+//                        9,800 125 / 105 (64: 99), 10,200 perfect trees 105 / 94
+//                        (64: 80), 40,880 264 / 222 (64: 122)
+//   TreeRNN 512          J = 32: 510 54.6 / 70, 2,550 87.5 / 84.4, 9,800 252 /
+//                        165, 40,880 730 / 409 (J = 16: 714)
+//   DAG-RNN 256 (16)     100 nodes in one launch 69.8 / 64, 1,000 94 / 87
+//   DAG-RNN 512          1,000 179 / 147, 10,000 634 / 399 (J = 32: 220, 424)
+constexpr int kNarySplitMinRows = 1537, kTreeSplitMinRows = 2560, kTreeWideMinRows = 6144;
+static bool pick_slice_split(int cell, int H, int32_t N, int32_t K, int64_t units, bool fused, Instance &out) {
+  if (K != 2) return false;
+  if (cell == CORTEX_NARY_TREELSTM && H == 256 && !fused && N >= kNarySplitMinRows)
+    return units == 2 ? pick_split<CORTEX_NARY_TREELSTM, 256, 2>(out, N) : pick_split<CORTEX_NARY_TREELSTM, 256, 8>(out, N);
+  if (cell == CORTEX_TREE_RNN && H == 256 && !fused && N >= kTreeSplitMinRows)
+    return N >= kTreeWideMinRows ? pick_split<CORTEX_TREE_RNN, 256, 64>(out, N) : pick_split<CORTEX_TREE_RNN, 256, 16>(out, N);
+  if (cell == CORTEX_TREE_RNN && H == 512 && !fused && N >= kTreeSplitMinRows) return pick_split<CORTEX_TREE_RNN, 512, 32>(out, N);
+  if (cell == CELL_DAG && H == 256) return pick_split<CELL_DAG, 256, 16>(out, N, fused);
+  if (cell == CELL_DAG && H == 512) return pick_split<CELL_DAG, 512, 16>(out, N, fused);
+  return false;
+}
+
 // units per slice: the knob's value where an instance exists, else the default
-static bool pick(int cell, int H, int32_t N, bool cached, Instance &out) {
+static bool pick(int cell, int H, int32_t N, int32_t K, bool cached, Instance &out) {
   const int64_t units = knob(CORTEX_KNOB_FWD_SLICE_UNITS);
   // TreeRNN at H = 64: the whole batch in one workgroup while it fits LDS,
   // then one workgroup per tree, then hidden slices; the unroll knob forces
@@ -3305,10 +3330,6 @@ static bool pick(int cell, int H, int32_t N, bool cached, Instance &out) {
       return true;
     }
   }
-  if (cell == CORTEX_NARY_TREELSTM && H == 256 && units == 2) {
-    pick_slice<CORTEX_NARY_TREELSTM, 256, 2>(cached, out);
-    return true;
-  }
   // DAG-RNN at H = 256: four 64-unit slices for large batches (operand
   // re-reads dominate there), sixteen 16-unit slices for small ones (a
   // tile's contraction is 4x shorter, and small levels are latency-bound);
@@ -3323,22 +3344,25 @@ static bool pick(int cell, int H, int32_t N, bool cached, Instance &out) {
     out.level_range_ok = true;
     return true;
   }
-#define CORTEX_CASE(CELLID, HH)                                      \
+  if (pick_slice_split(cell, H, N, K, units, false, out)) return true;
+  if (cell == CORTEX_NARY_TREELSTM && H == 256 && units == 2) {
+    pick_slice<CORTEX_NARY_TREELSTM, 256, 2, false>(cached, out);
+    return true;
+  }
+#define CORTEX_CASE(CELLID, HH, UNCACHED)                             \
   if (cell == CELLID && H == HH) {                                    \
-    pick_slice<CELLID, HH, Cell<CELLID, HH>::J>(cached, out);         \
+    pick_slice<CELLID, HH, Cell<CELLID, HH>::J, UNCACHED>(cached, out); \
     return true;                                                      \
   }
-  CORTEX_CASE(CORTEX_TREE_RNN, 64)
-  CORTEX_CASE(CORTEX_TREE_RNN, 256)
-  CORTEX_CASE(CORTEX_NARY_TREELSTM, 64)
-  CORTEX_CASE(CORTEX_NARY_TREELSTM, 256)
-  CORTEX_CASE(CORTEX_CHILDSUM_TREELSTM, 64)
-  CORTEX_CASE(CORTEX_CHILDSUM_TREELSTM, 256)
-  CORTEX_CASE(CORTEX_CHILDSUM_TREELSTM, 512)
-  CORTEX_CASE(CORTEX_TREE_RNN, 512)
-  CORTEX_CASE(CELL_DAG, 64)
-  CORTEX_CASE(CELL_DAG, 256)
-  CORTEX_CASE(CELL_DAG, 512)
+  CORTEX_CASE(CORTEX_TREE_RNN, 256, false)
+  CORTEX_CASE(CORTEX_TREE_RNN, 512, false)
+  CORTEX_CASE(CORTEX_NARY_TREELSTM, 256, false)
+  CORTEX_CASE(CORTEX_TREE_RNN, 64, true)
+  CORTEX_CASE(CORTEX_NARY_TREELSTM, 64, true)
+  CORTEX_CASE(CORTEX_CHILDSUM_TREELSTM, 64, true)
+  CORTEX_CASE(CORTEX_CHILDSUM_TREELSTM, 256, true)
+  CORTEX_CASE(CORTEX_CHILDSUM_TREELSTM, 512, true)
+  CORTEX_CASE(CELL_DAG, 64, true)
 #undef CORTEX_CASE
   if ((cell == CORTEX_CHILDSUM_TREEGRU || cell == CORTEX_SIMPLE_TREEGRU) && (H == 64 || H == 256 || H == 512)) {
     const bool simple = cell == CORTEX_SIMPLE_TREEGRU;
@@ -3387,7 +3411,8 @@ static bool pick_fused(int cell, int H, int32_t N, int32_t K, Instance &out) {
     out.lds = (size_t)N * kLdsHStride * sizeof(float) + fused_struct_ints(N, K) * sizeof(int);
     return true;
   }
-  if ((cell == CORTEX_NARY_TREELSTM && (H == 64 || H == 256)) || (cell == CORTEX_TREE_RNN && (H == 256 || H == 512))) {
+  if ((cell == CORTEX_NARY_TREELSTM && (H == 64 || (H == 256 && N < kNarySplitMinRows))) ||
+      (cell == CORTEX_TREE_RNN && (H == 256 || H == 512))) {
     const int J = cell == CORTEX_NARY_TREELSTM ? 4 : 16;
     if ((units != 0 && units != J) || K != 2 || N > kMaxCachedRows) return false;
     if (cell == CORTEX_NARY_TREELSTM)
@@ -3400,17 +3425,17 @@ static bool pick_fused(int cell, int H, int32_t N, int32_t K, Instance &out) {
     out.lds = fused_lds_ints(N, K) * sizeof(int);
     return true;
   }
-  if (cell == CELL_DAG && (H == 64 || H == 256 || H == 512)) {
-    // the slice kernel with 16-unit slices (at H = 256 the batches below the
-    // 64-unit kernel's range)
+  if (cell == CELL_DAG && H == 64) {
     if ((units != 0 && units != 16) || K != 2 || N > kMaxCachedRows) return false;
-    if (H == 256 && units == 0 && N >= kDagWideMinRows) return false;
-    out.fn = H == 64 ? slice_forward_kernel<CELL_DAG, 64, 16, true, false, true>
-                     : (H == 256 ? slice_forward_kernel<CELL_DAG, 256, 16, true, false, true>
-                                 : slice_forward_kernel<CELL_DAG, 512, 16, true, false, true>);
+    out.fn = slice_forward_kernel<CELL_DAG, 64, 16, true, false, true>;
     out.J = 16;
     out.lds = fused_lds_ints(N, K) * sizeof(int);
     return true;
+  }
+  if (cell == CELL_DAG && (H == 256 || H == 512)) {
+    // (at H = 256 the batches below the 64-unit kernel's range)
+    if ((units != 0 && units != 16) || (H == 256 && units == 0 && N >= kDagWideMinRows)) return false;
+    return pick_slice_split(cell, H, N, K, units, true, out);
   }
   if (cell == CORTEX_MVRNN && (H == kMvD || H == kMvD2) && K == 2) {
     out.fn = H == kMvD ? mvrnn_forward_kernel<kMvD, true> : mvrnn_forward_kernel<kMvD2, true>;
@@ -3518,7 +3543,7 @@ static int launch_forward(int cell, int H, const cortex_lin_t *lin, FwdArgs &a, 
     if (!cached) dyn = 0;
   }
   if (!fused_children) {
-    if (!pick(cell, H, lin->num_nodes, cached, inst)) return CORTEX_E_INVAL;
+    if (!pick(cell, H, lin->num_nodes, lin->max_arity, cached, inst)) return CORTEX_E_INVAL;
     if (inst.lds != SIZE_MAX) dyn = inst.lds;
   }
   const int per_cu = cached_occupancy((const void *)inst.fn, inst.threads, dyn);

@@ -1,0 +1,740 @@
+// Forward kernels that contract on the bf16 matrix units with fp32 accuracy.
+//
+// Every fp32 operand x is split into three bf16 planes, x = p0 + p1 + p2 (each
+// the round-to-nearest bf16 of what the planes before it leave: exact for
+// normal values, 3 x 8 significant bits), and a product a*b is taken as the six
+// plane products of order 2^-16 and above,
+//   a0 b0  +  (a0 b1 + a1 b0 + a1 b1 + a0 b2 + a2 b0),
+// the first in an accumulator of its own.  The dropped terms are below 2^-26 of
+// |a b|, less than one fp32 rounding.  A 16x16x32 bf16 MFMA takes 16 cycles, so
+// 32 k cost 96 cycles against 256 on the fp32 MFMA (8 x 32), and the sums are
+// closer to the exact ones: against 64 bits, dot products of N(0,1) rows with
+// U(-0.05, 0.05) weights are off by 0.47e-7 / 0.84e-7 / 1.75e-7 (2-norm,
+// K = 64 / 256 / 1024) against 1.06e-7 / 2.04e-7 / 4.00e-7 for fp32 MFMA
+// chains, since the large products are rounded K/32 times instead of K/4.
+// (With all six products in one accumulator the unit's truncation of small
+// addends shows: 0.91e-7 / 2.3e-7 / 4.9e-7.)
+//
+// Values that round to infinity in bf16 (infinities, |x| >= 3.396e38) cannot be
+// split; where a tile's operands or the weights hold one, the tile's sums are
+// formed again from the fp32 values (rare, slow and plain).  NaN needs no such
+// path: it stays NaN in every plane.
+#pragma once
+
+namespace cortex {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+
+struct Split8 {
+  bf16x8 p0, p1, p2;
+};
+
+// Two values rounded to bf16 (the first in the low half), and what that leaves of them.
+__device__ __forceinline__ unsigned int bf16_pair(float a, float b) {
+  const floatx2 v = {a, b};
+  const bf16x2 r = __builtin_convertvector(v, bf16x2);
+  return __builtin_bit_cast(unsigned int, r);
+}
+__device__ __forceinline__ void bf16_rest(unsigned int pair, float &a, float &b) {
+  a -= as_float(pair << 16);
+  b -= as_float(pair & 0xFFFF0000u);
+}
+
+__device__ __forceinline__ Split8 split8(const float4 x, const float4 y) {
+  float v[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+  u32x4 p[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    unsigned int q[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      q[k] = bf16_pair(v[2 * k], v[2 * k + 1]);
+      if (i < 2) bf16_rest(q[k], v[2 * k], v[2 * k + 1]);
+    }
+    p[i] = u32x4{q[0], q[1], q[2], q[3]};
+  }
+  return Split8{__builtin_bit_cast(bf16x8, p[0]), __builtin_bit_cast(bf16x8, p[1]), __builtin_bit_cast(bf16x8, p[2])};
+}
+
+// f(integral_constant 0), ..., f(integral_constant N - 1): indices into register
+// arrays stay compile-time constants through nested lambdas (a loop variable
+// there would put the arrays in scratch memory).
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_impl(F f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
+// Largest magnitude (NaN ignored), and the magnitude from which it cannot be split.
+constexpr float kSplitLimit = 3.3961775e38f;
+__device__ __forceinline__ float max_abs(float m, const float4 v) {
+  return fmaxf(fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
+}
+
+__device__ __forceinline__ floatx4 mfma_bf16(bf16x8 a, bf16x8 b, floatx4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// 32 k of NT output tiles that share one A fragment: the six plane products,
+// issued product-major so that consecutive MFMAs write different accumulators.
+// between(i) runs after product i (0..5): loads placed there, one at a time, do
+// not queue up ahead of the MFMAs in the address unit (64 bytes per clock).
+template <int NT, typename Between>
+__device__ __forceinline__ void mfma_split(const Split8 &a, const Split8 (&w)[NT], floatx4 (&hi)[NT], floatx4 (&lo)[NT],
+                                           Between between) {
+  static_for<6>([&](auto i) __attribute__((always_inline)) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      if constexpr (i == 0) lo[nt] = mfma_bf16(a.p2, w[nt].p0, lo[nt]);
+      if constexpr (i == 1) lo[nt] = mfma_bf16(a.p1, w[nt].p1, lo[nt]);
+      if constexpr (i == 2) lo[nt] = mfma_bf16(a.p0, w[nt].p2, lo[nt]);
+      if constexpr (i == 3) lo[nt] = mfma_bf16(a.p1, w[nt].p0, lo[nt]);
+      if constexpr (i == 4) lo[nt] = mfma_bf16(a.p0, w[nt].p1, lo[nt]);
+      if constexpr (i == 5) hi[nt] = mfma_bf16(a.p0, w[nt].p0, hi[nt]);
+    }
+    between(i);
+  });
+}
+
+// Exclusive prefix sum of one value per thread over the workgroup; wsum
+// holds kFwdWaves + 1 ints of LDS.  Returns the exclusive sum, *total the sum.
+__device__ __forceinline__ int block_excl_scan(int v, int *wsum, int *total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) wsum[wave] = x;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int run = 0;
+    for (int w = 0; w < kFwdWaves; ++w) {
+      const int t = wsum[w];
+      wsum[w] = run;
+      run += t;
+    }
+    wsum[kFwdWaves] = run;
+  }
+  __syncthreads();
+  const int ex = wsum[wave] + x - v;
+  *total = wsum[kFwdWaves];
+  __syncthreads();
+  return ex;
+}
+
+// One block's four values: staged (two pairs of (value, tag) pairs) or plain.
+// (By value: a choice between elements of the operand arrays would be made on
+// their addresses and put the arrays in scratch memory.)
+__device__ __forceinline__ float4 pick_block(bool staged, u32x4 lo, u32x4 hi, u32x4 plain) {
+  const unsigned int a = staged ? lo.x : plain.x, b = staged ? lo.z : plain.y;
+  const unsigned int c = staged ? hi.x : plain.z, d = staged ? hi.z : plain.w;
+  return make_float4(as_float(a), as_float(b), as_float(c), as_float(d));
+}
+
+// ---------------------------------------------------------------------------
+// The tiles of a node group, listed in LDS at entry with the operand sources of
+// their rows, so that the level loop never reads the linearization and the next
+// tile's operands can be requested across a level boundary.  A record is
+//   row0, level end, level, level start (then -1 where a tile's operands cannot
+//   be split), codes[16][CODES]
+// (the codes of SrcCfg).  A group with more tiles than the list holds runs them
+// a listed chunk at a time.
+// ---------------------------------------------------------------------------
+template <int CODES>
+struct TileList {
+  static constexpr int kHead = 4, kInts = kHead + kTileM * CODES;
+};
+
+// Records the tiles [first, first + cap) of this group over the levels
+// [lo, hi) (row0 .. level; the codes are filled by the caller); returns the
+// group's tile count.  One level per thread per round.  off(l) is the first row
+// of level l; *bad is set when the offsets are not monotone from 0 to N.
+template <int INTS, typename Off>
+__device__ __forceinline__ int list_tiles(const Off &off, int L, int N, int lo, int hi, int group, int Q, int first, int cap,
+                                          int tid, int *list, int *wsum, int &bad) {
+  int total = 0;
+  for (int lb = 0; lb < L; lb += kFwdThreads) {
+    const int l = lb + tid;
+    int cnt = 0, r0 = 0, r1 = 0, uf = 0;
+    if (l < L) {
+      r0 = off(l);
+      r1 = off(l + 1);
+      const bool ok = r0 >= 0 && r1 >= r0 && r1 <= N && (l != 0 || r0 == 0) && (l != L - 1 || r1 == N);
+      if (!ok) bad = 1;
+      const int ntile = (ok && l >= lo && l < hi) ? (r1 - r0 + kTileM - 1) / kTileM : 0;
+      uf = ((group - l) % Q + Q) % Q;
+      cnt = uf < ntile ? (ntile - 1 - uf) / Q + 1 : 0;
+    }
+    int round_total;
+    const int pos = total + block_excl_scan(cnt, wsum, &round_total) - first;
+    for (int j = max(0, -pos); j < cnt && pos + j < cap; ++j) {
+      int *t = &list[(pos + j) * INTS];
+      t[0] = r0 + kTileM * (uf + j * Q);
+      t[1] = r1;
+      t[2] = l;
+      t[3] = r0;
+    }
+    total += round_total;
+  }
+  return total;
+}
+
+// ---------------------------------------------------------------------------
+// TreeRNN, N-ary TreeLSTM and DAG-RNN at H = 256 and 512.
+//
+// Partition: workgroup b owns hidden slice b / Q (J units, all their gates) and
+// node group b % Q, which takes the 16-row tiles u of level l with
+// (u + l) % Q == group; a group's slices sit on one XCD when Q is a multiple
+// of 8 (round-robin dispatch).  Wave w contracts H/4 columns of child slot w / 4
+// (and H/8 columns of the node input, DAG-RNN); its weight fragments stay in
+// registers, already split, for the whole launch.
+//
+// What bounds it: on narrow levels the chain of exchanges between workgroups
+// (about 2 us each) and the one tile's contraction; on wide ones the number of
+// tiles per group, and every slice loading the tile's operand rows again.  So
+// wide batches take wide slices (J = 16 or 64: fewer, fuller tiles per group and
+// fewer loads of each row), small ones narrow slices, whose tile costs less.
+//
+// Per tile: the input part, which waits for nothing; the wait for the children;
+// per 32 columns, the split of the operands, the request of the next tile's and
+// the MFMAs.  The eight partial sums meet in LDS, where four of the waves sum
+// them and apply the gates (waves 0-3 for even tiles, 4-7 for odd ones) while
+// the others go on to the next tile: one workgroup barrier per tile.
+//
+// A staged pair's first load, before any poll, carries no device-scope bit: the
+// slices of a group then share their XCD's L2, and a stale line only shows an
+// old tag, after which the polls are device-scope.
+// ---------------------------------------------------------------------------
+template <int CELL, int H, int J_>
+struct SplitDims {
+  static constexpr int J = J_, GATES = Cell<CELL, H>::GATES, GJ = GATES * J, NT = (GJ + 15) / 16;
+  static constexpr bool kDag = CELL == CELL_DAG;
+  static constexpr int CODES = SrcCfg<CELL>::SEGS;
+  static constexpr int KX = kDag ? H / 8 : 0, XS = KX / 32;          // input columns per wave, 32-column steps
+  static constexpr int KR = 2 * H / 8, RS = KR / 32;                  // recurrent columns per wave
+  // row stride of the partial sums: 4 rows apart is 16 banks apart, so neither
+  // the MFMA-layout writes nor the unit-major reads conflict
+  static constexpr int LDC = 16 * NT + 4;
+  static constexpr int kPairs = kTileM * J;                           // (row, unit) pairs of a tile
+  static constexpr int PP = kPairs > 256 ? kPairs / 256 : 1;          // pairs per epilogue thread
+  static constexpr int PARTS = kPairs < 256 ? 256 / kPairs : 1;       // threads per pair
+  static_assert(KR % 32 == 0 && (!kDag || KX % 32 == 0) && 4 * KR == H, "whole 32-column steps, one child slot per wave");
+  static_assert(PARTS <= 8 && H % J == 0 && J <= 64, "epilogue mapping");
+};
+
+// Bytes of dynamic LDS: the list; fused launches add the input row by node id
+// and the linearizer's arrays.
+template <int CODES>
+constexpr size_t split_list_bytes(int cap) { return (size_t)cap * TileList<CODES>::kInts * sizeof(int); }
+constexpr int kSplitCap = 128, kSplitFusedCap = 48;
+
+template <int CELL, int H, int J, bool kFused, bool kWeightsFromMemory = false>
+__global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
+  using D = SplitDims<CELL, H, J>;
+  using TL = TileList<D::CODES>;
+  constexpr int NT = D::NT, XS = D::XS, RS = D::RS, GATES = D::GATES, LDC = D::LDC, PP = D::PP, PARTS = D::PARTS;
+  constexpr int INTS = TL::kInts, HEAD = TL::kHead, CODES = D::CODES;
+  constexpr bool kDag = D::kDag, kLstm = CELL == CORTEX_NARY_TREELSTM, kLeafInputs = !kDag;
+  constexpr int kCap = kFused ? kSplitFusedCap : kSplitCap;
+  constexpr int CBUF = kFwdWaves * kTileM * LDC;
+
+  __shared__ __attribute__((aligned(16))) float C_s[2 * CBUF];
+  __shared__ int wsum[kFwdWaves + 1];
+  __shared__ int stop_s[2];
+  extern __shared__ int dyn[];
+  int *list = dyn;                              // [kCap][INTS]
+
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int i16 = lane & 15, g4 = lane >> 4;
+  const int Q = a.Q, slice = blockIdx.x / Q, group = blockIdx.x % Q;
+  const int hbase = slice * J, N = a.N, K = a.K;
+  const uint32_t tag = launch_tag(a.sync);      // read with the status: one round trip
+  const TagBuf hs(a.hs, (uint32_t)N * H * 8);
+  const TagBuf cs(a.cs, kLstm ? (uint32_t)N * H * 8 : 0u);
+  const InBuf xin(kDag ? (const void *)a.x : (const void *)a.x_table,
+                  kDag ? (uint32_t)N * H * 4 : (a.x_table ? (uint32_t)a.x_rows * H * 4 : 0u));
+  const int rslot = wave >> 2, rcol = D::KR * (wave & 3) + 4 * g4;    // child slot; lane's first column in it
+  const int xcol = D::KX * wave + 4 * g4;
+  // epilogue: unit ej, part epart of the eight partial sums, rows erow + 4 p
+  const int et = tid & 255, eside = tid >> 8;
+  const int ej = et % J, epart = J >= 16 ? 0 : (et & 15) / J;
+  const int erow = J == 64 ? et >> 6 : (J == 32 ? 8 * ((et >> 5) & 1) + (et >> 6) : 4 * ((et >> 4) & 3) + (et >> 6));
+
+  CORTEX_TRACE_KERNEL(0);
+  const int status0 = load_status(a.status);
+  if (tid < 2) stop_s[tid] = 0;
+
+  // ---- weights: fragment (step s, tile nt) = gate row 16 nt + i16, two
+  // 16-column blocks of the step's 32 columns, four columns of each per lane
+  auto wcol = [&](int s, int half) __attribute__((always_inline)) -> int {
+    const int o = 32 * s + 16 * half;
+    if (kDag) return s < XS ? xcol + o : H + rslot * H + rcol + o - 32 * XS;
+    return rslot * H + rcol + o;
+  };
+  auto wfrag = [&](int s, int nt, int half, int row) __attribute__((always_inline)) -> float4 {
+    return weight_slice_at<CELL, H, J>(a, hbase, 16 * nt + row, wcol(s, half));
+  };
+  constexpr int WS = kWeightsFromMemory ? 1 : XS + RS;
+  Split8 w[WS][NT];
+  float wmax = 0.f;
+  float bias[GATES];
+#pragma unroll
+  for (int g = 0; g < GATES; ++g) bias[g] = a.b[g * H + hbase + ej];
+  auto split_weights = [&](const float4 (&v)[WS][NT][2]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < WS; ++s)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        wmax = max_abs(max_abs(wmax, v[s][nt][0]), v[s][nt][1]);
+        w[s][nt] = split8(v[s][nt][0], v[s][nt][1]);
+      }
+  };
+
+  // ---- structure: the group's tiles and their operand sources ----
+  int L = 0, bad = 0, total = 0, listed = 0, off1 = 0;
+  SmallLin m;
+  int *xnode = dyn + kCap * INTS;               // fused: the input row by node id
+  auto row_of_slot = [&](int idx) __attribute__((always_inline)) -> int {
+    const int *t = &list[(idx / kTileM) * INTS];
+    const int row = t[0] + idx % kTileM;
+    return row < t[1] ? row : -1;
+  };
+  const int lvl_lo = kLeafInputs ? max(a.level_lo, 1) : a.level_lo;
+  auto fill_fused = [&](int tid) __attribute__((always_inline)) {
+    for (int idx = tid; idx < listed * kTileM; idx += kFwdThreads) {
+      const int row = row_of_slot(idx);
+      int *cd = &list[(idx / kTileM) * INTS + HEAD + (idx % kTileM) * CODES];
+      const int v = row >= 0 ? m.order[row] : -1;
+      if (kDag) cd[0] = v >= 0 ? -2 - v : -1;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        int c = (v >= 0 && s < K) ? m.ch[v * K + s] : -1;
+        if (c >= 0) {
+          const int cr = m.nrow[c];
+          c = (kLeafInputs && !(a.ablate & 2) && cr < off1) ? (xnode[c] >= 0 ? -2 - xnode[c] : -1) : cr;
+        }
+        cd[kDag ? s + 1 : s] = c;
+      }
+    }
+  };
+  // (three dependent loads per leaf child: child row, its node, its input row;
+  // every slot of the chunk at once, so they cost one chain per chunk)
+  auto fill_global = [&](int tid) __attribute__((always_inline)) {
+    for (int idx = tid; idx < listed * kTileM; idx += kFwdThreads) {
+      const int row = row_of_slot(idx);
+      const int *t = &list[(idx / kTileM) * INTS];
+      int *cd = const_cast<int *>(t) + HEAD + (idx % kTileM) * CODES;
+      int c[2] = {-1, -1}, v = -1;
+      if (row >= 0) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) c[s] = s < K ? a.child_rows[(size_t)row * K + s] : -1;
+        if (kDag) {
+          v = a.level_nodes[row];
+          if (v < 0 || v >= N) {
+            bad = 1;
+            v = -1;
+          }
+        }
+      }
+      if (kDag) cd[0] = v >= 0 ? -2 - v : -1;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        if (c[s] < -1 || c[s] >= t[3]) {         // a child must sit in a lower level
+          bad = 1;
+          c[s] = -1;
+        }
+        if (kLeafInputs && !(a.ablate & 2) && c[s] >= 0 && c[s] < off1) {     // a leaf child: its input row
+          const int lv = a.level_nodes[c[s]];
+          int xi = -1;
+          if (lv < 0 || lv >= N) bad = 1;
+          else xi = a.x_index[lv];
+          if (xi < -1 || xi >= a.x_rows) {
+            raise_status(a.status, CORTEX_ST_INPUT_RANGE);
+            xi = -1;
+          }
+          c[s] = xi >= 0 ? -2 - xi : -1;
+        }
+        cd[kDag ? s + 1 : s] = c[s];
+      }
+    }
+  };
+  auto list_chunk = [&](int first) __attribute__((always_inline)) {
+    // (opaque, so that nothing derived from it is kept in registers through the
+    // tile loop for the next chunk)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    if constexpr (kFused) {
+      total = list_tiles<INTS>([&](int l) { return l < L ? m.lcount[l] : N; }, L, N, lvl_lo, a.level_hi, group, Q, first,
+                               kCap, tid, list, wsum, bad);
+      listed = min(total - first, kCap);
+      __syncthreads();
+      fill_fused(tid);
+    } else {
+      total = list_tiles<INTS>([&](int l) { return a.level_offsets[l]; }, L, N, lvl_lo, a.level_hi, group, Q, first, kCap,
+                               tid, list, wsum, bad);
+      listed = min(total - first, kCap);
+      if (__syncthreads_or(bad)) return;
+      fill_global(tid);
+    }
+  };
+
+  // (fused: the weight loads and the input rows share the round trip of the
+  // linearizer's children)
+  float4 wv[WS][NT][2];
+  if constexpr (!kWeightsFromMemory) {
+#pragma unroll
+    for (int s = 0; s < WS; ++s)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) wv[s][nt][hf] = wfrag(s, nt, hf, i16);
+  }
+  if constexpr (kFused) {
+    static_assert(!kWeightsFromMemory, "the ablation has no fused launch");
+    int xi[kFusedPer];
+#pragma unroll
+    for (int k = 0; k < kFusedPer; ++k) {
+      const int v = tid + k * kFwdThreads;
+      xi[k] = (kLeafInputs && v < N) ? a.x_index[v] : -1;
+    }
+    L = small_linearize<kFwdThreads, kFusedPer>(a.children, N, K, a.status, xnode + N, m, fused_lin_stamps(a));
+    if (L == 0) return;
+    if (blockIdx.x == 0)
+      small_lin_emit<kFwdThreads>(m, N, K, L, a.o_num_levels, a.o_height, a.o_level_offsets, a.o_level_nodes, a.o_node_row,
+                                  a.o_child_rows);
+    CORTEX_TRACE_KERNEL(9);
+    if constexpr (kLeafInputs) {
+#pragma unroll
+      for (int k = 0; k < kFusedPer; ++k) {
+        const int v = tid + k * kFwdThreads;
+        if (v < N) {
+          int x = xi[k];
+          if (x < -1 || x >= a.x_rows) {
+            raise_status(a.status, CORTEX_ST_INPUT_RANGE);
+            x = -1;
+          }
+          xnode[v] = x;
+        }
+      }
+    }
+    off1 = L > 1 ? m.lcount[1] : N;
+    CORTEX_TRACE_KERNEL(10);
+    if (status0 != 0) return;
+  } else {
+    L = *a.num_levels;
+    if (status0 != 0) return;
+    if (L < 1 || L > N) {
+      raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
+      return;
+    }
+    off1 = a.level_offsets[1];
+  }
+  if constexpr (!kWeightsFromMemory) split_weights(wv);
+
+  int gave_up = 0, lvl = lvl_lo;
+  u32x4 flo[2 * RS], fhi[2 * RS];     // staged child pairs: block b = columns rcol + 16 b .. +3
+  u32x4 fp[kLeafInputs ? 2 * RS : 1]; // the same columns of a leaf child's input row
+  u32x4 xv[XS > 0 ? 2 * XS : 1];      // DAG-RNN input: columns xcol + 16 b .. +3
+  int cd = -1;                        // source code of this lane's row and child slot
+  u32x2 cc[2];                        // N-ary: the children's memory cells of this thread's next epilogue
+  int ce[2] = {-1, -1};
+
+  auto code = [&](const int *t, int i, int seg) __attribute__((always_inline)) -> int {
+    return t[0] + i < t[1] ? t[HEAD + i * CODES + seg] : -1;
+  };
+  // Requests of a tile's operands for source code c, one load each: every lane
+  // issues both kinds (an offset beyond the buffer reads zeros without touching
+  // memory), so nothing branches between the MFMAs they are placed among.
+  constexpr int kLoads = kLeafInputs ? 6 * RS : 4 * RS;
+  auto staged_off = [&](int c) __attribute__((always_inline)) -> uint32_t {
+    return c >= 0 ? (uint32_t)(c * H + rcol) * 8u : kNoSource;
+  };
+  auto plain_off = [&](int c) __attribute__((always_inline)) -> uint32_t {
+    return c <= -2 ? (uint32_t)((-2 - c) * H + rcol) * 4u : kNoSource;
+  };
+  auto issue_load = [&](uint32_t so, uint32_t po, auto k) __attribute__((always_inline)) {
+    constexpr int PER = kLeafInputs ? 3 : 2, b = k / PER;
+    if constexpr (k % PER == 0) flo[b] = hs.first2_at(so + 128u * b);
+    if constexpr (k % PER == 1) fhi[b] = hs.first2_at(so + 128u * b + 16u);
+    if constexpr (k % PER == 2) fp[b] = xin.load4(po + 64u * b);
+  };
+  auto block_ready = [&](int b) __attribute__((always_inline)) -> bool {
+    return flo[b].y == tag && flo[b].w == tag && fhi[b].y == tag && fhi[b].w == tag;
+  };
+  auto block_value = [&](auto b) __attribute__((always_inline)) -> float4 {
+    if constexpr (kLeafInputs) {
+      return pick_block(cd >= 0, flo[b], fhi[b], fp[b]);
+    } else {
+      return make_float4(as_float(flo[b].x), as_float(flo[b].z), as_float(fhi[b].x), as_float(fhi[b].z));
+    }
+  };
+  auto issue_x = [&](int c) __attribute__((always_inline)) {
+#pragma unroll
+    for (int b = 0; b < 2 * XS; ++b)
+      xv[b] = xin.load4(c <= -2 ? (uint32_t)(((-2 - c) * H + xcol + 16 * b) * 4) : kNoSource);
+  };
+  auto issue_cells = [&](const int *t, int e) __attribute__((always_inline)) {
+    if (kLstm && eside == (e & 1)) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int c = code(t, erow, s);
+        ce[s] = c >= 0 ? c * H + hbase + ej : -1;
+        cc[s] = cs.load1_at(ce[s] >= 0 ? (uint32_t)ce[s] * 8u : kNoSource);
+      }
+    }
+  };
+  auto ready = [&](int e) __attribute__((always_inline)) -> bool {
+    bool r = true;
+#pragma unroll
+    for (int b = 0; b < 2 * RS; ++b) r = r && block_ready(b);
+    r = r || cd < 0;
+    if (kLstm && eside == (e & 1)) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) r = r && (ce[s] < 0 || cc[s].y == tag);
+    }
+    return r;
+  };
+
+  // One gate row's sum over every column of tile row i, from the fp32 values.
+  auto fp32_sum = [&](const int *t, int i, int gate_row) __attribute__((always_inline)) -> float {
+    float sum = 0.f;
+#pragma unroll 1
+    for (int c = 0; c < CODES * H; c += 4) {
+      const int src = code(t, i, c / H), o = c % H;
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (src >= 0) {
+        const uint32_t so = (uint32_t)(src * H + o) * 8u;
+        const u32x4 lo = hs.load2_at(so), hi = hs.load2_at(so + 16u);
+        v = make_float4(as_float(lo.x), as_float(lo.z), as_float(hi.x), as_float(hi.z));
+      } else if (src <= -2) {
+        v = as_float4(xin.load4((uint32_t)((-2 - src) * H + o) * 4u));
+      }
+      const float4 w4 = weight_slice_at<CELL, H, J>(a, hbase, gate_row, c);
+      sum = fmaf(v.x, w4.x, fmaf(v.y, w4.y, fmaf(v.z, w4.z, fmaf(v.w, w4.w, sum))));
+    }
+    return sum;
+  };
+
+  for (int first = 0;; first += kCap) {
+    if (first > 0) {
+      if (first >= total) break;
+      __syncthreads();                        // every wave is done with the last chunk's records
+    }
+    list_chunk(first);
+    if (!kFused && first == 0) {
+      if (kLeafInputs && !bad && (size_t)(4 * N + 1) * sizeof(int) <= kStructCacheBudget) {
+        // small batches: every row and input index is checked, also those that
+        // no tile reads
+#pragma unroll 1
+        for (int r = blockIdx.x * kFwdThreads + tid; r < N; r += gridDim.x * kFwdThreads) {
+          const int v = a.level_nodes[r], xi = a.x_index[r];
+          bool ok = v >= 0 && v < N;
+          for (int s = 0; s < K; ++s) {
+            const int c = a.child_rows[(size_t)r * K + s];
+            ok = ok && c >= -1 && (c < 0 || r >= off1);
+          }
+          if (!ok) raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
+          if (xi < -1 || xi >= a.x_rows) raise_status(a.status, CORTEX_ST_INPUT_RANGE);
+        }
+      }
+    }
+    if (__syncthreads_or(bad)) {
+      raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
+      return;
+    }
+    if (first == 0) {
+      CORTEX_TRACE_KERNEL(1);
+      CORTEX_TRACE_KERNEL(2);
+      if (!mark_entered(a.sync, tag, a.status)) return;
+    }
+    if (listed > 0) {
+      cd = code(list, i16, kDag ? 1 + rslot : rslot);
+      static_for<kLoads>([&](auto k) __attribute__((always_inline)) { issue_load(staged_off(cd), plain_off(cd), k); });
+      if (kDag) issue_x(code(list, i16, 0));
+      issue_cells(list, 0);
+    }
+    if (kLeafInputs && first == 0 && a.level_lo == 0) {
+      // the leaf level: h = input row, c = 0 (its loads and stores overlap the
+      // first tile's requests; no tile waits for these rows)
+      if constexpr (kFused) {
+        constexpr int H4 = H / 4;
+        for (int e = blockIdx.x * kFwdThreads + tid; e < off1 * H4; e += gridDim.x * kFwdThreads) {
+          const int xr = xnode[m.order[e / H4]];
+          *(float4 *)&a.h[(size_t)e * 4] =
+              as_float4(xin.load4(xr >= 0 ? (uint32_t)(xr * H + 4 * (e % H4)) * 4u : kNoSource));
+          if (kLstm) *(float4 *)&a.c[(size_t)e * 4] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+      } else {
+        write_leaf_outputs<H, kLstm>(a, nullptr, off1, hs, cs, tag);
+      }
+    }
+    for (int e = 0; e < listed; ++e) {
+      const int *t = &list[e * INTS], *tn = &list[(e + 1 < listed ? e + 1 : e) * INTS];
+      const bool more = e + 1 < listed;
+      const int l = t[2];
+      if (a.level_barrier) {
+        for (; lvl < l; ++lvl)
+          if (!grid_sync<false>(SyncWords{a.sync}, a.status, a.timeout)) return;
+      }
+      CORTEX_TRACE_POINT(l, 0);
+      floatx4 hi[NT], lo[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) hi[nt] = lo[nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+      float mx = wmax;
+      // 32 columns of step s: v0, v1 are this lane's four columns of its two blocks
+      auto contract = [&](auto s, const float4 v0, const float4 v1, auto between) __attribute__((always_inline)) {
+        if constexpr (kWeightsFromMemory) {
+          Split8 wm[NT];
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) {
+            const float4 w0 = wfrag(s, nt, 0, i16), w1 = wfrag(s, nt, 1, i16);
+            mx = max_abs(max_abs(mx, w0), w1);
+            wm[nt] = split8(w0, w1);
+          }
+          mfma_split<NT>(split8(v0, v1), wm, hi, lo, between);
+        } else {
+          mfma_split<NT>(split8(v0, v1), w[s], hi, lo, between);
+        }
+      };
+      if constexpr (kDag) {
+#pragma unroll
+        for (int b = 0; b < 2 * XS; ++b) mx = max_abs(mx, as_float4(xv[b]));
+        static_for<XS>([&](auto s) __attribute__((always_inline)) {
+          contract(s, as_float4(xv[2 * s]), as_float4(xv[2 * s + 1]), [](auto) {});
+        });
+        issue_x(more ? code(tn, i16, 0) : -1);
+      }
+      CORTEX_TRACE_POINT(l, 1);
+      if (!gave_up && !ready(e)) {
+        const uint64_t t0 = wall_clock64();
+        for (;;) {
+          __builtin_amdgcn_s_sleep(1);
+#pragma unroll
+          for (int b = 0; b < 2 * RS; ++b)
+            if (cd >= 0 && !block_ready(b)) {
+              flo[b] = hs.load2_at(staged_off(cd) + 128u * b);
+              fhi[b] = hs.load2_at(staged_off(cd) + 128u * b + 16u);
+            }
+          if (kLstm && eside == (e & 1)) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+              if (ce[s] >= 0 && cc[s].y != tag) cc[s] = cs.load1_at((uint32_t)ce[s] * 8u);
+          }
+          const int stv = load_status(a.status);
+          if (ready(e)) break;
+          if (stv != 0) {
+            gave_up = 1;
+            break;
+          }
+          if (wall_clock64() - t0 > a.timeout) {
+            raise_status(a.status, CORTEX_ST_BARRIER_TIMEOUT);
+            gave_up = 1;
+            break;
+          }
+        }
+        if (gave_up) stop_s[e & 1] = 1;      // read by every wave after this tile's barrier
+      }
+      CORTEX_TRACE_POINT(l, 2);
+      {
+        const int cdn = more ? code(tn, i16, kDag ? 1 + rslot : rslot) : -1;
+        const uint32_t so = staged_off(cdn), po = plain_off(cdn);
+        if (more) issue_cells(tn, e + 1);        // (for the other half's epilogue: not this tile's)
+        // the next tile's operands are requested between a step's products, into the
+        // registers whose values the step took
+        static_for<RS>([&](auto s) __attribute__((always_inline)) {
+          const float4 v0 = block_value(std::integral_constant<int, 2 * s>{}), v1 = block_value(std::integral_constant<int, 2 * s + 1>{});
+          mx = max_abs(max_abs(mx, v0), v1);
+          contract(std::integral_constant<int, XS + s>{}, v0, v1, [&](auto i) __attribute__((always_inline)) {
+            // this step's loads, spread over its six products
+            constexpr int PER = kLoads / RS, first = PER * s + PER * i / 6, last = PER * s + PER * (i + 1) / 6;
+            static_for<last - first>([&](auto k) __attribute__((always_inline)) {
+              issue_load(so, po, std::integral_constant<int, first + k>{});
+            });
+          });
+        });
+        cd = cdn;
+        if (mx >= kSplitLimit) list[e * INTS + 3] = -1;     // read after the tile's barrier
+      }
+      CORTEX_TRACE_WAVE(l);
+      float *cb = &C_s[(e & 1) * CBUF];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) cb[(wave * kTileM + 4 * g4 + v) * LDC + 16 * nt + i16] = hi[nt][v] + lo[nt][v];
+      __syncthreads();
+      CORTEX_TRACE_POINT(l, 3);
+      if (stop_s[e & 1]) return;             // a wave gave up its wait: every wave stops here
+      if (eside == (e & 1)) {
+        // the eight partial sums in one order whatever J is, then the bias
+        float z[PP][GATES];
+#pragma unroll
+        for (int p = 0; p < PP; ++p)
+#pragma unroll
+          for (int g = 0; g < GATES; ++g) {
+            const float *c0 = &cb[(erow + 4 * p) * LDC + g * J + ej];
+            float q[kFwdWaves];
+#pragma unroll
+            for (int k = 0; k < kFwdWaves / PARTS; ++k) q[k] = c0[(epart * (kFwdWaves / PARTS) + k) * kTileM * LDC];
+#pragma unroll
+            for (int n = kFwdWaves / PARTS; n > 1; n /= 2)
+#pragma unroll
+              for (int k = 0; k < n / 2; ++k) q[k] = q[2 * k] + q[2 * k + 1];
+#pragma unroll
+            for (int x = 1; x < PARTS; x *= 2) q[0] += __shfl_xor(q[0], J * x);
+            z[p][g] = bias[g] + q[0];
+          }
+        if (__builtin_expect(t[3] < 0, 0)) {
+          // an operand or a weight cannot be split: the sums in plain fp32
+#pragma unroll
+          for (int p = 0; p < PP; ++p)
+#pragma unroll
+            for (int g = 0; g < GATES; ++g) z[p][g] = bias[g] + fp32_sum(t, erow + 4 * p, g * J + ej);
+        }
+        if constexpr (kLstm) {
+          const int row = t[0] + erow;
+          const float cn = sigmoidf(z[0][0]) * tanh_f(z[0][4]) + sigmoidf(z[0][1]) * as_float(cc[0].x) +
+                           sigmoidf(z[0][2]) * as_float(cc[1].x);
+          const float hv = sigmoidf(z[0][3]) * tanh_f(cn);
+          if (epart == 0 && row < t[1]) {
+            const uint32_t el = (uint32_t)(row * H + hbase + ej);
+            cs.store1(el, cn, tag);
+            hs.store1(el, hv, tag);
+            a.c[el] = cn;
+            a.h[el] = hv;
+          }
+        } else {
+          float hv[PP];
+#pragma unroll
+          for (int p = 0; p < PP; ++p) hv[p] = tanh_f(z[p][0]);
+#pragma unroll
+          for (int p = 0; p < PP; ++p) {
+            const int row = t[0] + erow + 4 * p;
+            if (epart == 0 && row < t[1]) hs.store1((uint32_t)(row * H + hbase + ej), hv[p], tag);
+          }
+#pragma unroll
+          for (int p = 0; p < PP; ++p) {
+            const int row = t[0] + erow + 4 * p;
+            if (epart == 0 && row < t[1]) a.h[(size_t)row * H + hbase + ej] = hv[p];
+          }
+        }
+      }
+      CORTEX_TRACE_POINT(l, 4);
+      CORTEX_TRACE_POINT(l, 5);
+    }
+  }
+  if (a.level_barrier) {
+    for (const int last = min(L, a.level_hi) - 1; lvl < last; ++lvl)
+      if (!grid_sync<false>(SyncWords{a.sync}, a.status, a.timeout)) return;
+  }
+  CORTEX_TRACE_KERNEL(3);
+  if (a.retire) retire_tag(a.sync, tag, a.status, a.timeout);
+}
+
+}  // namespace cortex

@@ -1,0 +1,120 @@
+"""Kernels that contract split operands (three bf16 planes) on the bf16 matrix
+units: batch sizes on both sides of every rule that selects them, tiles with
+remainders, groups whose tile list runs in several chunks, operands and weights
+that cannot be split, and the accuracy of the sums themselves.  GPU."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from gpu_helpers import announce, compare_states, need_gpu
+
+torch = pytest.importorskip("torch")
+
+from oracle import cortex_oracle as O
+from paper_2011_01383_amd import cortex as C
+from paper_2011_01383_amd import inputs as I
+from paper_2011_01383_amd.runner import DeviceWorkload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    need_gpu()
+
+
+def run(wl):
+    dw = DeviceWorkload(wl)
+    dw.step()
+    assert dw.status_code() == 0
+    return dw
+
+
+def tree_rnn(seed, batch, lo, hi, H):
+    return I.tree_rnn_forest_workload(seed, batch=batch, H=H, leaf_lo=lo, leaf_hi=hi)
+
+
+# the last size of one rule and the first of the next (a binary tree of n leaves
+# has 2n - 1 nodes), odd sizes, and chains whose groups hold more tiles than one
+# list chunk
+SIZES = {
+    "nary_h256_1535": lambda: I.nary_treelstm_workload(1, batch=1, H=256, leaf_lo=768, leaf_hi=768),
+    "nary_h256_1537": lambda: I.nary_treelstm_workload(2, batch=1, H=256, leaf_lo=769, leaf_hi=769),
+    "nary_h256_4001": lambda: I.nary_treelstm_workload(3, batch=1, H=256, leaf_lo=2001, leaf_hi=2001),
+    "tree_rnn_h256_2559": lambda: I.tree_rnn_workload(4, n_leaves=1280, H=256),
+    "tree_rnn_h256_2561": lambda: I.tree_rnn_workload(5, n_leaves=1281, H=256),
+    "tree_rnn_h256_6143": lambda: I.tree_rnn_workload(6, n_leaves=3072, H=256),
+    "tree_rnn_h256_6145": lambda: I.tree_rnn_workload(7, n_leaves=3073, H=256),
+    "tree_rnn_h256_forest": lambda: tree_rnn(8, 211, 3, 61, 256),
+    "tree_rnn_h512_2561": lambda: I.tree_rnn_workload(9, n_leaves=1281, H=512),
+    "dag_h256_1x1": lambda: I.dagrnn_workload(10, n_grids=1, rows=1, cols=1, H=256),
+    "dag_h512_33x17": lambda: I.dagrnn_workload(11, n_grids=5, rows=33, cols=17, H=512),
+}
+
+
+@pytest.mark.parametrize("name", sorted(SIZES))
+def test_sizes(name):
+    wl = SIZES[name]()
+    announce("split %s N=%d" % (name, wl.N))
+    compare_states(run(wl).states_by_node(), O.forward_workload(wl), name)
+
+
+def _caterpillars(seed, batch, n_leaves):
+    """N-ary TreeLSTM over chain-shaped trees: one node per tree and level."""
+    wl = I.nary_treelstm_workload(seed, batch=1, H=256, leaf_lo=batch * n_leaves, leaf_hi=batch * n_leaves)
+    children, is_leaf = I.forest_to_children([I.caterpillar(n_leaves, left_spine=bool(i & 1)) for i in range(batch)], 2)
+    x_index = np.full(is_leaf.size, -1, dtype=np.int32)
+    x_index[is_leaf] = np.random.default_rng(seed).integers(0, 1000, size=int(is_leaf.sum()))
+    return dataclasses.replace(wl, children=children, x_index=x_index)
+
+
+@pytest.mark.parametrize("groups", [0, 1])
+def test_more_tiles_than_the_list(groups):
+    """450 levels of one tile each: with one node group its 449 tiles take
+    four chunks of the list (128 tiles)."""
+    wl = _caterpillars(12, 4, 450)
+    announce("split caterpillars groups %d N=%d" % (groups, wl.N))
+    C.cortex_set_knob(C.CORTEX_KNOB_FWD_NODE_GROUPS, groups)
+    try:
+        got = run(wl).states_by_node()
+    finally:
+        C.cortex_set_knob(C.CORTEX_KNOB_FWD_NODE_GROUPS, 0)
+    compare_states(got, O.forward_workload(wl), "caterpillars")
+
+
+UNSPLITTABLE = {
+    "nary": lambda: I.nary_treelstm_workload(20, batch=60, H=256, leaf_lo=20, leaf_hi=20),
+    "tree_rnn": lambda: tree_rnn(21, 60, 30, 30, 256),
+    "dag_h256": lambda: I.dagrnn_workload(22, n_grids=3, rows=5, cols=4, H=256),
+    "dag_h512": lambda: I.dagrnn_workload(23, n_grids=2, rows=5, cols=4, H=512),
+}
+
+
+@pytest.mark.parametrize("value", [float("inf"), 3.4e38, -3.397e38, float("nan")])
+@pytest.mark.parametrize("where", ["input", "weight"])
+@pytest.mark.parametrize("name", sorted(UNSPLITTABLE))
+def test_unsplittable_values(name, where, value):
+    """One infinite, NaN or near-overflow input element or weight: the states
+    are those of the definition (the gates saturate; NaN spreads to the same
+    nodes and units)."""
+    wl = UNSPLITTABLE[name]()
+    announce("split %s %s %r N=%d" % (name, where, value, wl.N))
+    if where == "input":
+        key = "x" if wl.x is not None else "x_table"
+        arr = getattr(wl, key).copy()
+        arr[3, 5] = value
+    else:
+        key = "U" if wl.U is not None else "W"
+        arr = getattr(wl, key).copy()
+        arr.reshape(-1, wl.H)[7, 9] = value
+    wl = dataclasses.replace(wl, **{key: arr})
+    got = run(wl).states_by_node()
+    with np.errstate(all="ignore"):
+        ref = O.forward_workload(wl)
+    for key in ref:
+        r32 = ref[key].astype(np.float32).astype(np.float64)       # fp64 states beyond the fp32 range
+        assert np.array_equal(np.isnan(got[key]), np.isnan(r32)), key
+        fine = np.isfinite(r32)
+        assert np.array_equal(got[key][~fine & ~np.isnan(r32)], r32[~fine & ~np.isnan(r32)]), key
+        assert float(np.abs(got[key][fine] - r32[fine]).max()) <= 1e-4 * max(1.0, float(np.abs(r32[fine]).max())), key
