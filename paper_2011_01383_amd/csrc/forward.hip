@@ -3247,7 +3247,7 @@ static void pick_slice(bool cached, Instance &out) {
   out.threads = kFwdThreads;
   out.level_barrier_ok = out.level_range_ok = true;
   if constexpr (CELL == CORTEX_CHILDSUM_TREELSTM) {
-    out.fn = cached ? childsum_forward_kernel<H, true> : childsum_forward_kernel<H, false>;
+    out.fn = kUncached && !cached ? childsum_forward_kernel<H, !kUncached> : childsum_forward_kernel<H, true>;
   } else {
     const bool from_memory = knob(CORTEX_KNOB_ABLATE) & 1;      // the instance without model persistence
     if (kUncached && !cached)
@@ -3302,6 +3302,13 @@ static bool pick_slice_split(int cell, int H, int32_t N, int32_t K, int64_t unit
   if (cell == CELL_DAG && H == 512) return pick_split<CELL_DAG, 512, 16>(out, N, fused);
   return false;
 }
+
+// Child-sum TreeLSTM at H = 256: the split kernel from this size on, in two
+// launches (us per step, fp32 kernel / split: 800 nodes in one launch 62.9 /
+// 68.6, 1,250 82.9 / 79.6, 2,000 132 / 93, 10,000 496 / 248).  At H = 512 a
+// slice of 4 units is all its registers hold, and the fp32 kernel is faster
+// (500 nodes 107 / 145, 3,000 495 / 552).
+constexpr int kChildsumSplitMinRows = 1200;
 
 // units per slice: the knob's value where an instance exists, else the default
 static bool pick(int cell, int H, int32_t N, int32_t K, bool cached, Instance &out) {
@@ -3360,7 +3367,15 @@ static bool pick(int cell, int H, int32_t N, int32_t K, bool cached, Instance &o
   CORTEX_CASE(CORTEX_TREE_RNN, 64, true)
   CORTEX_CASE(CORTEX_NARY_TREELSTM, 64, true)
   CORTEX_CASE(CORTEX_CHILDSUM_TREELSTM, 64, true)
-  CORTEX_CASE(CORTEX_CHILDSUM_TREELSTM, 256, true)
+  if (cell == CORTEX_CHILDSUM_TREELSTM && H == 256 && N >= kChildsumSplitMinRows) {
+    out.fn = childsum_split_kernel;
+    out.J = ChildsumSplit::J;
+    out.threads = kFwdThreads;
+    out.lds = split_list_bytes<ChildsumSplit::CODES>(ChildsumSplit::kCap);
+    out.level_barrier_ok = out.level_range_ok = true;
+    return true;
+  }
+  CORTEX_CASE(CORTEX_CHILDSUM_TREELSTM, 256, false)
   CORTEX_CASE(CORTEX_CHILDSUM_TREELSTM, 512, true)
   CORTEX_CASE(CELL_DAG, 64, true)
 #undef CORTEX_CASE
@@ -3448,6 +3463,7 @@ static bool pick_fused(int cell, int H, int32_t N, int32_t K, Instance &out) {
   if ((cell == CORTEX_CHILDSUM_TREELSTM || gru) && (H == 64 || H == 256 || H == 512)) {
     if (units != 0 && units != 4) return false;
     const bool simple = cell == CORTEX_SIMPLE_TREEGRU;
+    if (!gru && H == 256 && N >= kChildsumSplitMinRows) return false;
     if (!gru)
       out.fn = H == 64 ? childsum_forward_kernel<64, true, true>
                        : (H == 256 ? childsum_forward_kernel<256, true, true> : childsum_forward_kernel<512, true, true>);

@@ -618,7 +618,7 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
           __builtin_amdgcn_s_sleep(1);
 #pragma unroll
           for (int b = 0; b < 2 * RS; ++b)
-            if (cd >= 0 && !block_ready(b)) {
+            if (__any(cd >= 0 && !block_ready(b))) {       // (the whole wave: no masks to carry)
               flo[b] = hs.load2_at(staged_off(cd) + 128u * b);
               fhi[b] = hs.load2_at(staged_off(cd) + 128u * b + 16u);
             }
@@ -713,6 +713,7 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
           float hv[PP];
 #pragma unroll
           for (int p = 0; p < PP; ++p) hv[p] = tanh_f(z[p][0]);
+          // the tagged pairs (what the next level waits for) first, then the outputs
 #pragma unroll
           for (int p = 0; p < PP; ++p) {
             const int row = t[0] + erow + 4 * p;
@@ -723,6 +724,551 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
             const int row = t[0] + erow + 4 * p;
             if (epart == 0 && row < t[1]) a.h[(size_t)row * H + hbase + ej] = hv[p];
           }
+        }
+      }
+      CORTEX_TRACE_POINT(l, 4);
+      CORTEX_TRACE_POINT(l, 5);
+    }
+  }
+  if (a.level_barrier) {
+    for (const int last = min(L, a.level_hi) - 1; lvl < last; ++lvl)
+      if (!grid_sync<false>(SyncWords{a.sync}, a.status, a.timeout)) return;
+  }
+  CORTEX_TRACE_KERNEL(3);
+  if (a.retire) retire_tag(a.sync, tag, a.status, a.timeout);
+}
+
+// ---------------------------------------------------------------------------
+// Child-sum TreeLSTM at H = 256, batches beyond one launch (8 units per slice).
+//
+// Gate rows of a slice: (i, o | u, f) x 8, in two output tiles.  Wave w contracts
+// 32 columns of the node input and of each of the four child slots, all slots of
+// a row in one lane: the child sum h~ is then a sum of registers, and the first
+// tile contracts h~ once instead of every child (seven products of 16 x 16 x 32
+// per wave and tile; every slot with every gate would be ten).  The last tile
+// contracts each slot: its f columns are U_f h_k, and its u columns sum over the
+// slots to U_u h~.  An absent slot reads zeros.  The input weights' planes sit in
+// LDS, the recurrent ones in registers beside the operands of two tiles.
+//
+// Leaves (more than half of the nodes) have no child: they run first, 64 rows
+// per step, on their inputs alone.  The rest is as in slice_split_kernel.
+//
+// What bounds it: the operand loads, 16 per wave and tile through the address
+// unit (0.85 us of a tile's 5), the two waves of a SIMD taking turns on the
+// matrix unit and the vector ALU, and the epilogue of the waves on duty.  200
+// trees (10,000 nodes) 496 -> 248 us per step against the fp32 kernel's 4-unit
+// slices, which re-read every child row 64 times; 40 trees 132 -> 93.
+// ---------------------------------------------------------------------------
+struct ChildsumSplit {
+  static constexpr int H = 256, J = 8, NT = J / 4, HT = NT - 1;               // gate tiles; those without f
+  static constexpr int KW = H / 8, RS = KW / 32;                      // columns per wave of x and of each slot
+  static constexpr int UB = 16 * HT, FB = UB + 16 - J;                // partial-sum columns: sums, then f_k
+  static constexpr int COLS = FB + 4 * J, LDC = (COLS - 4 + 15) / 16 * 16 + 4;
+  static constexpr int PARTS = 256 / (kTileM * J);
+  static constexpr int CODES = 5, INTS = TileList<CODES>::kInts, HEAD = TileList<CODES>::kHead;
+  static constexpr int LEAF = 64, LDL = 28;             // rows per leaf step, their partial-sum stride
+  static constexpr int CBUF = kFwdWaves * kTileM * LDC;
+  // the split input weights, in LDS: [step][tile][plane][wave][lane] x 16 bytes
+  static constexpr int kWx = RS * NT * 3 * kFwdThreads;
+  static constexpr int kCap = 64;
+  static_assert(J % 4 == 0 && J <= 8 && KW % 32 == 0 && kFwdWaves * LEAF * LDL <= 2 * CBUF, "tiling");
+};
+
+__global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) {
+  using D = ChildsumSplit;
+  constexpr int CELL = CORTEX_CHILDSUM_TREELSTM, H = D::H, J = D::J;
+  constexpr int NT = D::NT, HT = D::HT, RS = D::RS, LDC = D::LDC, PARTS = D::PARTS, INTS = D::INTS, HEAD = D::HEAD;
+  constexpr int CODES = D::CODES, CBUF = D::CBUF, LEAF = D::LEAF, LDL = D::LDL;
+  constexpr int kCap = D::kCap;
+
+  __shared__ __attribute__((aligned(16))) float C_s[2 * CBUF];
+  __shared__ u32x4 Wx_s[D::kWx];
+  __shared__ int wsum[kFwdWaves + 1];
+  __shared__ int stop_s[2], big_s[2];
+  __shared__ float bias_s[4 * J];
+  extern __shared__ int dyn[];
+  int *list = dyn;                              // [kCap][INTS]; the leaf rows' inputs before that
+
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int i16 = lane & 15, g4 = lane >> 4;
+  const int Q = a.Q, slice = blockIdx.x / Q, group = blockIdx.x % Q;
+  const int hbase = slice * J, N = a.N, K = a.K;
+  const uint32_t tag = launch_tag(a.sync);      // read with the status: one round trip
+  const TagBuf hs(a.hs, (uint32_t)N * H * 8);
+  const TagBuf cs(a.cs, (uint32_t)N * H * 8);
+  const InBuf xin(a.x_table, a.x_table ? (uint32_t)a.x_rows * H * 4 : 0u);
+  const int col = D::KW * wave + 4 * g4;        // this lane's first column of x and of every child
+  const int et = tid & 255, eside = tid >> 8;
+  const int ej = et % J, epart = (et & 15) / J, erow = 4 * ((et >> 4) & 3) + (et >> 6);
+
+  CORTEX_TRACE_KERNEL(0);
+  const int status0 = load_status(a.status);
+  if (tid < 2) stop_s[tid] = big_s[tid] = 0;
+
+  auto wfrag = [&](int sg, int s, int nt, int half) __attribute__((always_inline)) -> float4 {
+    return weight_slice_at<CELL, H, J>(a, hbase, 16 * nt + i16, sg * H + col + 32 * s + 16 * half);
+  };
+  float4 wv[2][RS][NT][2];
+#pragma unroll
+  for (int sg = 0; sg < 2; ++sg)
+#pragma unroll
+    for (int s = 0; s < RS; ++s)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) wv[sg][s][nt][hf] = wfrag(sg, s, nt, hf);
+  if (tid < 4 * J) bias_s[tid] = a.b[childsum_gate(tid / J) * H + hbase + tid % J];     // i, o, u, f
+
+  int bad = 0;
+  const int L = *a.num_levels;
+  if (status0 != 0) return;
+  if (L < 1 || L > N) {
+    raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
+    return;
+  }
+  const int off1 = a.level_offsets[1];
+  if (off1 < 1 || off1 > N) {
+    raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
+    return;
+  }
+  Split8 wu[RS][NT];
+  float wmax = 0.f;
+#pragma unroll
+  for (int s = 0; s < RS; ++s)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+      for (int sg = 0; sg < 2; ++sg) wmax = max_abs(max_abs(wmax, wv[sg][s][nt][0]), wv[sg][s][nt][1]);
+      // (each lane reads back only what it wrote: no barrier)
+      const Split8 x = split8(wv[0][s][nt][0], wv[0][s][nt][1]);
+      u32x4 *o = &Wx_s[(s * NT + nt) * 3 * kFwdThreads + tid];
+      o[0] = __builtin_bit_cast(u32x4, x.p0);
+      o[kFwdThreads] = __builtin_bit_cast(u32x4, x.p1);
+      o[2 * kFwdThreads] = __builtin_bit_cast(u32x4, x.p2);
+      wu[s][nt] = split8(wv[1][s][nt][0], wv[1][s][nt][1]);
+    }
+
+  auto wx = [&](int s, Split8 (&w)[NT]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const u32x4 *o = &Wx_s[(s * NT + nt) * 3 * kFwdThreads + tid];
+      w[nt] = Split8{__builtin_bit_cast(bf16x8, o[0]), __builtin_bit_cast(bf16x8, o[kFwdThreads]),
+                     __builtin_bit_cast(bf16x8, o[2 * kFwdThreads])};
+    }
+  };
+  // The input row of row r, -1 = none (validated).
+  auto input_row = [&](int r) __attribute__((always_inline)) -> int {
+    const int v = a.level_nodes[r];
+    if (v < 0 || v >= N) {
+      bad = 1;
+      return -1;
+    }
+    const int xi = a.x_index[v];
+    if (xi < -1 || xi >= a.x_rows) {
+      raise_status(a.status, CORTEX_ST_INPUT_RANGE);
+      return -1;
+    }
+    return xi;
+  };
+  // Plain fp32 dot products, for rows or weights that cannot be split: gate row
+  // m of segment sg (0: W with input row r, 1: U with staged row r).
+  auto fp32_dot = [&](int sg, int r, int gate_row) __attribute__((always_inline)) -> float {
+    float sum = 0.f;
+    if (r < 0) return sum;
+#pragma unroll 1
+    for (int c = 0; c < H; c += 4) {
+      float4 v;
+      if (sg == 1) {
+        const uint32_t so = (uint32_t)(r * H + c) * 8u;
+        const u32x4 lo = hs.load2_at(so), hi = hs.load2_at(so + 16u);
+        v = make_float4(as_float(lo.x), as_float(lo.z), as_float(hi.x), as_float(hi.z));
+      } else {
+        v = as_float4(xin.load4((uint32_t)(r * H + c) * 4u));
+      }
+      const float4 w4 = weight_slice_at<CELL, H, J>(a, hbase, gate_row, sg * H + c);
+      sum = fmaf(v.x, w4.x, fmaf(v.y, w4.y, fmaf(v.z, w4.z, fmaf(v.w, w4.w, sum))));
+    }
+    return sum;
+  };
+  // Tree sum of this thread's part of the eight partial sums at c0 (stride:
+  // floats between waves), then over the parts of the pair: one order whatever J.
+  auto sum_parts = [&](const float *c0, int stride) __attribute__((always_inline)) -> float {
+    float q[kFwdWaves];
+#pragma unroll
+    for (int k = 0; k < kFwdWaves / PARTS; ++k) q[k] = c0[(epart * (kFwdWaves / PARTS) + k) * stride];
+#pragma unroll
+    for (int n = kFwdWaves / PARTS; n > 1; n /= 2)
+#pragma unroll
+      for (int k = 0; k < n / 2; ++k) q[k] = q[2 * k] + q[2 * k + 1];
+#pragma unroll
+    for (int x = 1; x < PARTS; x *= 2) q[0] += __shfl_xor(q[0], J * x);
+    return q[0];
+  };
+
+  if (!mark_entered(a.sync, tag, a.status)) return;
+  CORTEX_TRACE_KERNEL(1);
+  CORTEX_TRACE_KERNEL(2);
+
+  // ---- level 0: c = i*u, h = o*tanh(c) on the inputs alone; step n of the
+  // group takes the rows [64 (group + n Q), + 64)
+  if (a.level_lo == 0) {
+    constexpr int MT = LEAF / kTileM;
+    const int nsteps = (off1 + LEAF - 1) / LEAF, mine = group < nsteps ? (nsteps - 1 - group) / Q + 1 : 0;
+    constexpr int kChunk = kCap * INTS / LEAF;          // steps whose input rows the list holds
+#pragma unroll 1
+    for (int first = 0; first < mine; first += kChunk) {
+      const int cnt = min(mine - first, kChunk);
+      if (first > 0) __syncthreads();
+#pragma unroll 1
+      for (int idx = tid; idx < cnt * LEAF; idx += kFwdThreads) {
+        const int row = LEAF * (group + (first + idx / LEAF) * Q) + idx % LEAF;
+        list[idx] = row < off1 ? input_row(row) : -1;
+      }
+      if (__syncthreads_or(bad)) {
+        raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
+        return;
+      }
+      u32x4 xl[MT][2 * RS];
+      auto issue_leaf = [&](int n) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+          const int xr = n < cnt ? list[n * LEAF + t * kTileM + i16] : -1;
+          const uint32_t o = xr >= 0 ? (uint32_t)(xr * H + col) * 4u : kNoSource;
+#pragma unroll
+          for (int b = 0; b < 2 * RS; ++b) xl[t][b] = xin.load4(o + 64u * b);
+        }
+      };
+      issue_leaf(0);
+#pragma unroll 1
+      for (int n = 0; n < cnt; ++n) {
+        const int rowbase = LEAF * (group + (first + n) * Q);
+        float mx = wmax;
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+          floatx4 hi[NT], lo[NT];
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) hi[nt] = lo[nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+          static_for<RS>([&](auto s) __attribute__((always_inline)) {
+            const float4 v0 = as_float4(xl[t][2 * s]), v1 = as_float4(xl[t][2 * s + 1]);
+            mx = max_abs(max_abs(mx, v0), v1);
+            Split8 w[NT];
+            wx(s, w);
+            mfma_split<NT>(split8(v0, v1), w, hi, lo, [](auto) {});
+          });
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt)
+            if (16 * nt + i16 < 3 * J)
+#pragma unroll
+              for (int v = 0; v < 4; ++v)
+                C_s[(wave * LEAF + t * kTileM + 4 * g4 + v) * LDL + 16 * nt + i16] = hi[nt][v] + lo[nt][v];
+        }
+        issue_leaf(n + 1);
+        if (mx >= kSplitLimit) big_s[n & 1] = 1;
+        __syncthreads();
+        const bool big = big_s[n & 1] != 0;
+        if (tid < LEAF * J) {
+          const int j = tid % J, i = tid / J, row = rowbase + i;
+          float z[3];
+#pragma unroll
+          for (int g = 0; g < 3; ++g) {
+            const float *c0 = &C_s[i * LDL + g * J + j];
+            float q[kFwdWaves];
+#pragma unroll
+            for (int k = 0; k < kFwdWaves; ++k) q[k] = c0[k * LEAF * LDL];
+#pragma unroll
+            for (int w = kFwdWaves; w > 1; w /= 2)
+#pragma unroll
+              for (int k = 0; k < w / 2; ++k) q[k] = q[2 * k] + q[2 * k + 1];
+            z[g] = bias_s[g * J + j] + q[0];
+          }
+          if (__builtin_expect(big, 0)) {
+#pragma unroll 1
+            for (int g = 0; g < 3; ++g) {
+              const float sum = bias_s[g * J + j] + fp32_dot(0, list[n * LEAF + i], g * J + j);
+              if (g == 0) z[0] = sum;
+              if (g == 1) z[1] = sum;
+              if (g == 2) z[2] = sum;
+            }
+          }
+          if (row < off1) {
+            const float cn = sigmoidf(z[0]) * tanh_f(z[2]), hv = sigmoidf(z[1]) * tanh_f(cn);
+            const uint32_t el = (uint32_t)(row * H + hbase + j);
+            cs.store1(el, cn, tag);
+            hs.store1(el, hv, tag);
+            a.c[el] = cn;
+            a.h[el] = hv;
+          }
+        }
+        if (tid == 0) big_s[(n + 1) & 1] = 0;
+        __syncthreads();                     // the partial sums may be overwritten
+      }
+    }
+    if (L > 1 && a.level_hi > 1 && a.level_barrier && !grid_sync<false>(SyncWords{a.sync}, a.status, a.timeout)) return;
+  }
+
+  int gave_up = 0, lvl = max(a.level_lo, 1);
+  u32x4 flo[4][2], fhi[4][2];         // child slot k, block b of a 32-column step
+  u32x4 xv[2 * RS];
+  int cd[4];                          // this lane's row: child rows, -1 = none
+  u32x2 cc[4];                        // the children's memory cells of this thread's next epilogue
+  unsigned int cmask = 0u;            // which of them exist
+
+  auto code = [&](const int *t, int i, int k) __attribute__((always_inline)) -> int {
+    return t[0] + i < t[1] ? t[HEAD + i * CODES + k] : -1;
+  };
+  auto child_off = [&](int c) __attribute__((always_inline)) -> uint32_t {
+    return c >= 0 ? (uint32_t)(c * H + col) * 8u : kNoSource;
+  };
+  auto issue_slot = [&](uint32_t so, auto k, auto q) __attribute__((always_inline)) {     // load q (0..3) of slot k
+    if constexpr (q % 2 == 0) flo[k][q / 2] = hs.first2_at(so + 128u * (q / 2));
+    else fhi[k][q / 2] = hs.first2_at(so + 128u * (q / 2) + 16u);
+  };
+  auto issue_x = [&](int c) __attribute__((always_inline)) {
+    const uint32_t o = c >= 0 ? (uint32_t)(c * H + col) * 4u : kNoSource;
+#pragma unroll
+    for (int b = 0; b < 2 * RS; ++b) xv[b] = xin.load4(o + 64u * b);
+  };
+  auto issue_cells = [&](const int *t, int e) __attribute__((always_inline)) {
+    if (eside == (e & 1)) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int c = code(t, erow, k);
+        cmask = k == 0 ? (c >= 0) : cmask | (unsigned int)(c >= 0) << k;
+        cc[k] = cs.load1_at(c >= 0 ? (uint32_t)(c * H + hbase + ej) * 8u : kNoSource);
+      }
+    }
+  };
+
+  int total = 0, listed = 0;
+#pragma unroll 1
+  for (int first = 0;; first += kCap) {
+    if (first > 0 && first >= total) break;
+    __syncthreads();                          // every wave is done with the records (or the leaf inputs)
+    {
+      // (opaque, so that nothing derived from it is kept through the tile loop)
+      int t0 = threadIdx.x;
+      asm volatile("" : "+v"(t0));
+      total = list_tiles<INTS>([&](int l) { return a.level_offsets[l]; }, L, N, max(a.level_lo, 1), a.level_hi, group, Q, first,
+                               kCap, t0, list, wsum, bad);
+      listed = min(total - first, kCap);
+      if (__syncthreads_or(bad)) {
+        raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
+        return;
+      }
+#pragma unroll 1
+      for (int idx = t0; idx < listed * kTileM; idx += kFwdThreads) {
+        int *t = &list[(idx / kTileM) * INTS], *o = t + HEAD + (idx % kTileM) * CODES;
+        const int row = t[0] + idx % kTileM;
+        const bool live = row < t[1];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          int c = -1;
+          if (live && s < K) {
+            c = a.child_rows[(size_t)row * K + s];
+            if (c < -1 || c >= t[3]) {        // a child must sit in a lower level
+              bad = 1;
+              c = -1;
+            }
+          }
+          o[s] = c;
+        }
+        o[4] = live ? input_row(row) : -1;
+      }
+      if (first == 0 && ((size_t)N * (K + 2) + 1) * sizeof(int) <= kStructCacheBudget) {
+        // small batches: a leaf with children is refused
+#pragma unroll 1
+        for (int r = blockIdx.x * kFwdThreads + t0; r < off1; r += gridDim.x * kFwdThreads)
+          for (int s = 0; s < K; ++s)
+            if (a.child_rows[(size_t)r * K + s] != -1) raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
+      }
+    }
+    if (__syncthreads_or(bad)) {
+      raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
+      return;
+    }
+    if (listed > 0) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) cd[k] = code(list, i16, k);
+      static_for<4>([&](auto k) __attribute__((always_inline)) {
+        static_for<4>([&](auto q) __attribute__((always_inline)) { issue_slot(child_off(cd[k]), k, q); });
+      });
+      issue_x(code(list, i16, 4));
+      issue_cells(list, 0);
+    }
+#pragma unroll 1
+    for (int e = 0; e < listed; ++e) {
+      const int *t = &list[e * INTS], *tn = &list[(e + 1 < listed ? e + 1 : e) * INTS];
+      const bool more = e + 1 < listed;
+      const int l = t[2];
+      if (a.level_barrier) {
+        for (; lvl < l; ++lvl)
+          if (!grid_sync<false>(SyncWords{a.sync}, a.status, a.timeout)) return;
+      }
+      CORTEX_TRACE_POINT(l, 0);
+      float mx = wmax;
+      // the input part waits for nothing
+      floatx4 hi[NT], lo[NT];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) hi[nt] = lo[nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+      static_for<RS>([&](auto s) __attribute__((always_inline)) {
+        const float4 v0 = as_float4(xv[2 * s]), v1 = as_float4(xv[2 * s + 1]);
+        mx = max_abs(max_abs(mx, v0), v1);
+        Split8 w[NT];
+        wx(s, w);
+        mfma_split<NT>(split8(v0, v1), w, hi, lo, [](auto) {});
+      });
+      issue_x(more ? code(tn, i16, 4) : -1);
+      CORTEX_TRACE_POINT(l, 1);
+      floatx4 fh[4][1], fl[4][1];         // (the last step leaves the sum in fh)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) fh[k][0] = fl[k][0] = floatx4{0.f, 0.f, 0.f, 0.f};
+      int cdn[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) cdn[k] = more ? code(tn, i16, k) : -1;
+      static_for<RS>([&](auto s) __attribute__((always_inline)) {
+        // wait for step s of every child slot (and, before the first, the cells)
+        auto slot_ready = [&](int k) __attribute__((always_inline)) -> bool {
+          return cd[k] < 0 || (flo[k][0].y == tag && flo[k][0].w == tag && fhi[k][0].y == tag && fhi[k][0].w == tag &&
+                               flo[k][1].y == tag && flo[k][1].w == tag && fhi[k][1].y == tag && fhi[k][1].w == tag);
+        };
+        auto ready = [&]() __attribute__((always_inline)) -> bool {
+          bool r = true;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) r = r && slot_ready(k);
+          if (s == RS - 1 && eside == (e & 1)) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) r = r && (!((cmask >> k) & 1u) || cc[k].y == tag);
+          }
+          return r;
+        };
+        if (!gave_up && !ready()) {
+          const uint64_t t0 = wall_clock64();
+          for (;;) {
+            __builtin_amdgcn_s_sleep(1);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+              if (__any(!slot_ready(k))) {       // (the whole wave: no masks to carry)
+                const uint32_t so = child_off(cd[k]) + 256u * s;
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                  flo[k][b] = hs.load2_at(so + 128u * b);
+                  fhi[k][b] = hs.load2_at(so + 128u * b + 16u);
+                }
+              }
+            if (s == RS - 1 && eside == (e & 1)) {
+#pragma unroll
+              for (int k = 0; k < 4; ++k)
+                if (((cmask >> k) & 1u) && cc[k].y != tag)
+                  cc[k] = cs.load1_at((uint32_t)(code(t, erow, k) * H + hbase + ej) * 8u);
+            }
+            const int stv = load_status(a.status);
+            if (ready()) break;
+            if (stv != 0) {
+              gave_up = 1;
+              break;
+            }
+            if (wall_clock64() - t0 > a.timeout) {
+              raise_status(a.status, CORTEX_ST_BARRIER_TIMEOUT);
+              gave_up = 1;
+              break;
+            }
+          }
+          if (gave_up) stop_s[e & 1] = 1;    // read by every wave after this tile's barrier
+        }
+        CORTEX_TRACE_POINT(l, 2);
+        float4 h0 = make_float4(0.f, 0.f, 0.f, 0.f), h1 = h0;     // h~ of this lane's columns
+        static_for<4>([&](auto k) __attribute__((always_inline)) {
+          const float4 v0 = make_float4(as_float(flo[k][0].x), as_float(flo[k][0].z), as_float(fhi[k][0].x), as_float(fhi[k][0].z));
+          const float4 v1 = make_float4(as_float(flo[k][1].x), as_float(flo[k][1].z), as_float(fhi[k][1].x), as_float(fhi[k][1].z));
+          // (an absent slot's loads read zeros)
+          mx = max_abs(max_abs(mx, v0), v1);
+          if constexpr (HT > 0) {
+            h0 = make_float4(h0.x + v0.x, h0.y + v0.y, h0.z + v0.z, h0.w + v0.w);
+            h1 = make_float4(h1.x + v1.x, h1.y + v1.y, h1.z + v1.z, h1.w + v1.w);
+          }
+          // the slot's next operands: the tile's next 32 columns, or the next tile's first
+          const uint32_t so = s + 1 < RS ? child_off(cd[k]) + 256u * (s + 1) : child_off(cdn[k]);
+          Split8 wl[1] = {wu[s][NT - 1]};
+          mfma_split<1>(split8(v0, v1), wl, fh[k], fl[k], [&](auto i) __attribute__((always_inline)) {
+            if constexpr (i < 4) issue_slot(so, k, i);
+          });
+          if constexpr (s == RS - 1) fh[k][0] += fl[k][0];
+        });
+        if constexpr (HT > 0) {
+          mx = max_abs(max_abs(mx, h0), h1);
+          mfma_split<HT>(split8(h0, h1), reinterpret_cast<const Split8(&)[HT]>(wu[s]), reinterpret_cast<floatx4(&)[HT]>(hi),
+                         reinterpret_cast<floatx4(&)[HT]>(lo), [](auto) {});
+        }
+      });
+      if (mx >= kSplitLimit) list[e * INTS + 3] = -1;     // read after the tile's barrier
+      CORTEX_TRACE_WAVE(l);
+      float *cb = &C_s[(e & 1) * CBUF];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float *c0 = &cb[(wave * kTileM + 4 * g4 + v) * LDC];
+#pragma unroll
+        for (int nt = 0; nt < HT; ++nt) c0[16 * nt + i16] = hi[nt][v] + lo[nt][v];
+        const float x = hi[NT - 1][v] + lo[NT - 1][v];
+        float f[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f[k] = fh[k][0][v];
+        if (i16 < 16 - J) {
+          c0[D::UB + i16] = x + ((f[0] + f[1]) + (f[2] + f[3]));
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) c0[D::FB + k * J + i16 - (16 - J)] = x + f[k];
+        }
+      }
+      // (the cells of the next tile go to the other half of the waves)
+      if (more) issue_cells(tn, e + 1);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) cd[k] = cdn[k];
+      __syncthreads();
+      CORTEX_TRACE_POINT(l, 3);
+      if (stop_s[e & 1]) return;             // a wave gave up its wait: every wave stops here
+      if (eside == (e & 1)) {
+        const float *c0 = &cb[erow * LDC + ej];
+        constexpr int WST = kTileM * LDC;
+        float z[3], f[4];
+#pragma unroll
+        for (int g = 0; g < 3; ++g) z[g] = bias_s[g * J + ej] + sum_parts(c0 + g * J, WST);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f[k] = bias_s[3 * J + ej] + sum_parts(c0 + D::FB + k * J, WST);
+        if (__builtin_expect(t[3] < 0, 0)) {
+          // an operand or a weight cannot be split: the sums in plain fp32
+          const int xr = code(t, erow, 4);
+#pragma unroll 1
+          for (int g = 0; g < 4; ++g) {
+            float sum = fp32_dot(0, xr, g * J + ej);
+            if (g == 3) f[0] = f[1] = f[2] = f[3] = sum;
+#pragma unroll 1
+            for (int k = 0; k < 4; ++k) {
+              const float d = fp32_dot(1, code(t, erow, k), g * J + ej);
+              sum += d;
+              if (g == 3) {
+                if (k == 0) f[0] = bias_s[3 * J + ej] + (f[0] + d);
+                if (k == 1) f[1] = bias_s[3 * J + ej] + (f[1] + d);
+                if (k == 2) f[2] = bias_s[3 * J + ej] + (f[2] + d);
+                if (k == 3) f[3] = bias_s[3 * J + ej] + (f[3] + d);
+              }
+            }
+            if (g == 0) z[0] = bias_s[0 * J + ej] + sum;
+            if (g == 1) z[1] = bias_s[1 * J + ej] + sum;
+            if (g == 2) z[2] = bias_s[2 * J + ej] + sum;
+          }
+        }
+        float fc[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) fc[k] = (cmask >> k) & 1u ? sigmoidf(f[k]) * as_float(cc[k].x) : 0.f;
+        const float cn = sigmoidf(z[0]) * tanh_f(z[2]) + ((fc[0] + fc[1]) + (fc[2] + fc[3]));
+        const float hv = sigmoidf(z[1]) * tanh_f(cn);
+        const int row = t[0] + erow;
+        if (epart == 0 && row < t[1]) {
+          const uint32_t el = (uint32_t)(row * H + hbase + ej);
+          cs.store1(el, cn, tag);
+          hs.store1(el, hv, tag);
+          a.c[el] = cn;
+          a.h[el] = hv;
         }
       }
       CORTEX_TRACE_POINT(l, 4);

@@ -35,6 +35,10 @@ def tree_rnn(seed, batch, lo, hi, H):
     return I.tree_rnn_forest_workload(seed, batch=batch, H=H, leaf_lo=lo, leaf_hi=hi)
 
 
+def childsum(seed, batch, lo, hi, max_arity=4):
+    return I.childsum_treelstm_workload(seed, batch=batch, H=256, node_lo=lo, node_hi=hi, max_arity=max_arity)
+
+
 # the last size of one rule and the first of the next (a binary tree of n leaves
 # has 2n - 1 nodes), odd sizes, and chains whose groups hold more tiles than one
 # list chunk
@@ -48,6 +52,11 @@ SIZES = {
     "tree_rnn_h256_6145": lambda: I.tree_rnn_workload(7, n_leaves=3073, H=256),
     "tree_rnn_h256_forest": lambda: tree_rnn(8, 211, 3, 61, 256),
     "tree_rnn_h512_2561": lambda: I.tree_rnn_workload(9, n_leaves=1281, H=512),
+    "childsum_h256_1199": lambda: childsum(13, 1, 1199, 1199),
+    "childsum_h256_1200": lambda: childsum(14, 1, 1200, 1200),
+    "childsum_h256_arity2": lambda: childsum(15, 40, 30, 90, max_arity=2),
+    "childsum_h256_all_leaves": lambda: childsum(16, 1201, 1, 1),
+    "childsum_h256_forest": lambda: childsum(17, 333, 1, 60),
     "dag_h256_1x1": lambda: I.dagrnn_workload(10, n_grids=1, rows=1, cols=1, H=256),
     "dag_h512_33x17": lambda: I.dagrnn_workload(11, n_grids=5, rows=33, cols=17, H=512),
 }
@@ -69,6 +78,27 @@ def _caterpillars(seed, batch, n_leaves):
     return dataclasses.replace(wl, children=children, x_index=x_index)
 
 
+@pytest.mark.parametrize("groups", [0, 1, 3])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_childsum_schedules_agree(mode, groups):
+    """Node groups and level orderings change the schedule only: bitwise the
+    default's states; one group has more tiles and leaves than its list."""
+    wl = childsum(18, 60, 20, 80)
+    announce("split childsum mode %d groups %d N=%d" % (mode, groups, wl.N))
+    ref = run(wl).states_by_node()
+    C.cortex_set_knob(C.CORTEX_KNOB_LEVEL_SYNC, mode)
+    C.cortex_set_knob(C.CORTEX_KNOB_FWD_NODE_GROUPS, groups)
+    try:
+        got = run(wl).states_by_node()
+    finally:
+        C.cortex_set_knob(C.CORTEX_KNOB_LEVEL_SYNC, 0)
+        C.cortex_set_knob(C.CORTEX_KNOB_FWD_NODE_GROUPS, 0)
+    for key in ref:
+        assert np.array_equal(ref[key], got[key]), key
+    if mode == 0 and groups == 0:
+        compare_states(ref, O.forward_workload(wl), "childsum")
+
+
 @pytest.mark.parametrize("groups", [0, 1])
 def test_more_tiles_than_the_list(groups):
     """450 levels of one tile each: with one node group its 449 tiles take
@@ -85,6 +115,7 @@ def test_more_tiles_than_the_list(groups):
 
 UNSPLITTABLE = {
     "nary": lambda: I.nary_treelstm_workload(20, batch=60, H=256, leaf_lo=20, leaf_hi=20),
+    "childsum": lambda: childsum(24, 80, 20, 20),
     "tree_rnn": lambda: tree_rnn(21, 60, 30, 30, 256),
     "dag_h256": lambda: I.dagrnn_workload(22, n_grids=3, rows=5, cols=4, H=256),
     "dag_h512": lambda: I.dagrnn_workload(23, n_grids=2, rows=5, cols=4, H=512),
@@ -105,7 +136,8 @@ def test_unsplittable_values(name, where, value):
         arr = getattr(wl, key).copy()
         arr[3, 5] = value
     else:
-        key = "U" if wl.U is not None else "W"
+        # (child-sum: an input weight; its leaves have no recurrent product to meet one of U)
+        key = "U" if wl.U is not None and wl.cell != I.CELL_CHILDSUM_TREELSTM else "W"
         arr = getattr(wl, key).copy()
         arr.reshape(-1, wl.H)[7, 9] = value
     wl = dataclasses.replace(wl, **{key: arr})
