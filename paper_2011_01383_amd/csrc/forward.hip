@@ -1210,109 +1210,10 @@ __global__ void __launch_bounds__(kFwdThreads) tree_rnn_lds_kernel(FwdArgs a) {
   CORTEX_TRACE_KERNEL(3);
 }
 
-// ---------------------------------------------------------------------------
-// DAG-RNN at H = 256 with four hidden slices of 64 units:
-//   h(v) = tanh(W x(v) + U_0 h(slot 0) + U_1 h(slot 1) + b).
-// Fewer, wider slices than the kernel above: every slice re-reads the child
-// rows it contracts, so four slices move a quarter of the operand bytes of
-// sixteen.  Each wave keeps its 64 recurrent columns x 64 units of U_0 / U_1
-// in registers for the whole launch and the input weights W sit in LDS.  When
-// the grid is a multiple of 32, the four slices of node group q are
-// workgroups 32m + r + 8s (r = q mod 8, m = q div 8, s = 0..3), which
-// round-robin dispatch places on one XCD, so the input row of a node is
-// fetched into one L2 once.
-//
-// Work is done in steps: a step is up to two of the group's 16-row tiles of
-// one level (group q owns the tiles u of level l with u = q - l mod Q, so a
-// level of up to 2Q tiles is one step per group).  The tiles of a step share
-// one wait, one cross-wave reduction and one epilogue, and every weight
-// fragment is read once for both tiles.  Per step, wave w
-//   1. contracts input columns [32w, 32w+32) (requested one step earlier;
-//      they depend on no child); between the MFMA steps of the first half it
-//      requests the next step's input fragments, and between those of the
-//      second half the child-state fragments of its recurrent columns
-//      [64w, 64w+64) of [h(slot 0) | h(slot 1)] for every row of the step,
-//   2. waits until every fragment it read carries this launch's tag,
-//   3. contracts the recurrent columns;
-// the eight partial sums then meet in LDS and the workgroup applies tanh and
-// writes the step's rows.  The next step's input fragments are complete
-// before the stores are issued, so no wait of the next step covers them.
-// A level of at most Q/2 tiles is split finer: each of its tiles is a half
-// step of two groups, one per half of the slice's units, so the narrow first
-// and last levels of a batch, whose chain of waits sets the pace, take half
-// the contraction time per group.  At entry each workgroup lists its steps of
-// every level with their operand sources in LDS, so the level loop never
-// goes back to the linearization in memory; a group with more steps than the
-// list holds (60) lists them a chunk at a time, the next chunk once it has
-// run the previous one.
-// ---------------------------------------------------------------------------
+// DAG-RNN at H = 256 (slice_split_kernel): 16-unit slices, 32-unit slices for
+// batches of at least kDagWideMinRows rows, 64-unit slices from kDag64MinRows.
 constexpr int kDagH = 256, kDagJ = 64, kDagS = kDagH / kDagJ;
-constexpr int kDagWideMinRows = 6144;              // default choice of this kernel (measured crossover)
-constexpr int kDagStepTiles = 2;                   // tiles per step
-constexpr int kDagStepRows = kDagStepTiles * kTileM;
-// level, level start, first row of tile 0, first row of tile 1 (-1: none),
-// level end, units (0: the slice's 64, 1: its first 32, 2: its last 32),
-// then codes[32][3]: -2 - node id (input row) or -1, child rows
-constexpr int kDagStepHead = 6;
-constexpr int kDagStepInts = kDagStepHead + kDagStepRows * 3;
-constexpr int kDagStepCap = 60;                    // steps per workgroup list (dynamic LDS)
-constexpr size_t kDagListBytes = (size_t)kDagStepCap * kDagStepInts * sizeof(int);
-
-// Tiles of group `group` at a level of ntile tiles; returns their count.
-// Normally the tiles u = uf, uf + Q, ... with uf = (group - l) mod Q, whole
-// (half = 0).  A level of at most Q/2 tiles (Q even) gives each tile to two
-// groups, each computing half of its slice's units, so the tile's
-// contraction is split over twice the compute units: group q takes tile
-// (q - l) mod Q as half 1 (the first 32 units) or tile (q - l + Q/2) mod Q
-// as half 2 (the last 32); at most one of the two exists.
-__device__ __forceinline__ int dag_group_tiles(int group, int l, int Q, int ntile, int &uf, int &half) {
-  const int u1 = ((group - l) % Q + Q) % Q;
-  half = 0;
-  uf = u1;
-  if (Q % 2 == 0 && 2 * ntile <= Q) {
-    const int u2 = (u1 + Q / 2) % Q;
-    if (u1 < ntile) {
-      half = 1;
-      return 1;
-    }
-    if (u2 < ntile) {
-      uf = u2;
-      half = 2;
-      return 1;
-    }
-    return 0;
-  }
-  return u1 < ntile ? (ntile - 1 - u1) / Q + 1 : 0;
-}
-
-// The row of slot (t, i) of a step record, or -1 when the slot is empty.
-__device__ __forceinline__ int dag_slot_row(const int *st, int slot) {
-  const int base = st[2 + slot / kTileM], row = base + slot % kTileM;
-  return (base >= 0 && row < st[4]) ? row : -1;
-}
-
-// Stores the operand sources of a slot from its row's node id v and child
-// rows c0, c1 (read when live, i.e. the slot holds a row), validated as the
-// forward requires (a child lies below its row's level); returns false when
-// the linearization is inconsistent.
-__device__ __forceinline__ bool dag_store_codes(const FwdArgs &a, int *st, int slot, bool live, int v, int c0, int c1) {
-  const int lstart = st[1];
-  int *cd = &st[kDagStepHead + slot * 3];
-  if (!live) v = c0 = c1 = -1;
-  bool ok = !live || (v >= 0 && v < a.N);
-  cd[0] = (v >= 0 && v < a.N) ? -2 - v : -1;
-  if (c0 < -1 || c0 >= lstart) {
-    ok = false;
-    c0 = -1;
-  }
-  if (c1 < -1 || c1 >= lstart) {
-    ok = false;
-    c1 = -1;
-  }
-  cd[1] = c0;
-  cd[2] = c1;
-  return ok;
-}
+constexpr int kDagWideMinRows = 6144, kDag64MinRows = 36864;
 
 // Hoisted input products of the DAG-RNN at H = 256 (the ablation of the
 // fused input part; Sec. 7.1 computes them with one matrix product before the
@@ -1378,462 +1279,6 @@ __global__ void __launch_bounds__(kFwdThreads) dag_input_gemm_kernel(FwdArgs a) 
       const int row = r0 + kTileM * wave + 4 * g4 + e;
       if (row < N) a.pre[(size_t)row * H + hbase + 16 * nt + i16] = acc[nt][e] + bias_s[16 * nt + i16];
     }
-}
-
-template <bool kHoisted>
-__global__ void __launch_bounds__(kFwdThreads) dag_slice64_kernel(FwdArgs a) {
-  constexpr int H = kDagH, J = kDagJ, NT = J / 16;
-  constexpr int KX = H / kFwdWaves, NBX = KX / 16;          // input columns per wave, 16-blocks
-  constexpr int KR = 2 * H / kFwdWaves, NBR = KR / 16;      // recurrent columns per wave, 16-blocks
-  constexpr int LDX = H + 4;                                // W row stride in LDS
-  // partial sums: C_s[wave][tile][column][16 rows], the four 16-byte row
-  // quarters of column c stored in the order q ^ ((c >> 2) & 3), so the
-  // 16-byte accesses of 16 consecutive columns meet 64 distinct banks
-  constexpr int MT = kDagStepTiles;
-  constexpr int SI = kDagStepInts;
-  constexpr int EPI = MT * kTileM * J / kFwdThreads;        // outputs per thread per full step
-  static_assert(NBX * 16 == KX && NBR * 16 == KR && EPI * kFwdThreads == MT * kTileM * J, "tiling");
-  static_assert(KR == 64 && H % KR == 0, "a wave's recurrent columns lie in one child slot");
-
-  __shared__ __attribute__((aligned(16))) float Wx_s[kHoisted ? 4 : J * LDX];
-  __shared__ __attribute__((aligned(16))) float C_s[kFwdWaves * MT * J * kTileM];
-  __shared__ int stop_s;
-  __shared__ float bias_s[J];
-  __shared__ int wsum[kFwdWaves + 1];
-  extern __shared__ int list[];               // [kDagStepCap][kDagStepInts]
-
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int i16 = lane & 15, g4 = lane >> 4;
-  const int bid = blockIdx.x;
-  const bool xcd_map = (gridDim.x & 31) == 0;
-  const int slice = xcd_map ? ((bid >> 3) & 3) : bid % kDagS;
-  const int group = xcd_map ? ((bid & 7) + 8 * (bid >> 5)) : bid / kDagS;
-  const int Q = a.Q;
-  const int hbase = slice * J;
-  const int N = a.N;
-  const uint32_t tag = launch_tag(a.sync);     // read with the status: one round trip
-  const TagBuf hs(a.hs, (uint32_t)N * H * 8);
-  const InBuf xin(a.x, kHoisted ? 0u : (uint32_t)N * H * 4);
-  const InBuf pin(a.pre, kHoisted ? (uint32_t)N * H * 4 : 0u);
-  const int rslot = wave >> 2;                 // child slot of this wave's recurrent columns
-  const int rcol = KR * (wave & 3);            // their first column within that child's h
-  const int xcol = KX * wave;                  // this wave's first input column
-
-  CORTEX_TRACE_KERNEL(0);
-  // The structure is read first and the weights (192 KB per workgroup, the
-  // longest transfer of the entry) are requested once the step list is
-  // known, after the operand sources' loads: vector loads complete in order,
-  // so weights requested first would hold back every structure read behind
-  // them.
-  const int status0 = load_status(a.status);
-  const int L = *a.num_levels;
-  if (tid == 0) stop_s = 0;
-  if (status0 != 0) return;
-  if (L < 1 || L > N) {
-    raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
-    return;
-  }
-
-  // ---- this group's steps of every level, one level per thread per round:
-  // the list holds steps [first, first + kDagStepCap) of them; returns the
-  // group's step count.  A group with more steps runs them in chunks,
-  // listing the next chunk once it has run the previous one.
-  auto list_steps = [&](int first, int &bad) __attribute__((always_inline)) -> int {
-    int total = 0;
-    for (int lb = 0; lb < L; lb += kFwdThreads) {
-      const int l = lb + tid;
-      int nst = 0, r0 = 0, r1 = 0, uf = 0, cnt = 0, half = 0;
-      if (l < L) {
-        r0 = a.level_offsets[l];
-        r1 = a.level_offsets[l + 1];
-        const bool ok = r0 >= 0 && r1 >= r0 && r1 <= N && (l != 0 || r0 == 0) && (l != L - 1 || r1 == N);
-        if (!ok) bad = 1;
-        const int ntile = (ok && l >= a.level_lo && l < a.level_hi) ? (r1 - r0 + kTileM - 1) / kTileM : 0;
-        cnt = dag_group_tiles(group, l, Q, ntile, uf, half);
-        nst = (cnt + MT - 1) / MT;
-      }
-      int round_total;
-      const int pos = total + block_excl_scan(nst, wsum, &round_total) - first;
-      for (int j = max(0, -pos); j < nst && pos + j < kDagStepCap; ++j) {
-        int *st = &list[(pos + j) * SI];
-        st[0] = l;
-        st[1] = r0;
-        st[2] = r0 + kTileM * (uf + (MT * j) * Q);
-        st[3] = MT * j + 1 < cnt ? r0 + kTileM * (uf + (MT * j + 1) * Q) : -1;
-        st[4] = r1;
-        st[5] = half;
-      }
-      total += round_total;
-    }
-    return total;
-  };
-  int bad = 0;
-  const int total = list_steps(0, bad);
-  // (each level's end is the next level's start, so the levels tile [0, N))
-  if (__syncthreads_or(bad)) {
-    raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
-    return;
-  }
-  int listed = min(total, kDagStepCap);        // steps in the list
-  // operand sources of every listed slot: requested now, stored below
-  constexpr int kFillPer = (kDagStepCap * kDagStepRows + kFwdThreads - 1) / kFwdThreads;
-  int frow[kFillPer], fv[kFillPer], f0[kFillPer], f1[kFillPer];
-#pragma unroll
-  for (int k = 0; k < kFillPer; ++k) {
-    const int idx = tid + k * kFwdThreads;
-    frow[k] = idx < listed * kDagStepRows ? dag_slot_row(&list[(idx / kDagStepRows) * SI], idx % kDagStepRows) : -1;
-    fv[k] = f0[k] = f1[k] = -1;
-    if (frow[k] >= 0) {
-      fv[k] = a.level_nodes[frow[k]];
-      f0[k] = a.child_rows[(size_t)frow[k] * 2];
-      f1[k] = a.child_rows[(size_t)frow[k] * 2 + 1];
-    }
-  }
-  // recurrent weights: wr[b][nt] = U_rslot[hbase + 16 nt + i16][rcol + 16 b + 4 g4 .. +3]
-  float4 wr[NBR][NT];
-#pragma unroll
-  for (int b = 0; b < NBR; ++b)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-      wr[b][nt] = *(const float4 *)(a.U + ((size_t)rslot * H + hbase + 16 * nt + i16) * H + rcol + 16 * b + 4 * g4);
-  constexpr int ITEMS = J * H / 4, PER = kHoisted ? 1 : ITEMS / kFwdThreads;
-  float4 v[PER];
-  if constexpr (!kHoisted) {
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int idx = tid + k * kFwdThreads;
-      v[k] = *(const float4 *)(a.W + (size_t)(hbase + idx / (H / 4)) * H + 4 * (idx % (H / 4)));
-    }
-    if (tid < J) bias_s[tid] = a.b[hbase + tid];
-  }
-#pragma unroll
-  for (int k = 0; k < kFillPer; ++k) {
-    const int idx = tid + k * kFwdThreads;
-    if (idx < listed * kDagStepRows &&
-        !dag_store_codes(a, &list[(idx / kDagStepRows) * SI], idx % kDagStepRows, frow[k] >= 0, fv[k], f0[k], f1[k]))
-      bad = 1;
-  }
-  if constexpr (!kHoisted) {
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int idx = tid + k * kFwdThreads;
-      *(float4 *)&Wx_s[(idx / (H / 4)) * LDX + 4 * (idx % (H / 4))] = v[k];
-    }
-  }
-  if (__syncthreads_or(bad)) {
-    raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
-    return;
-  }
-  CORTEX_TRACE_KERNEL(1);
-  CORTEX_TRACE_KERNEL(2);
-  if (!mark_entered(a.sync, tag, a.status)) return;
-  int gave_up = 0;
-
-  // input fragments of a step's rows (tile t, row i16): x[node][xcol + 16 b + 4 g4 .. +3]
-  // (live false: every load reads zeros, so a step without a successor still
-  // issues the same loads and the waits after them keep fixed counts)
-  auto x_offsets = [&](const int *st, bool live, uint32_t (&xo)[MT]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int t = 0; t < MT; ++t) {
-      const int base = st[2 + t];
-      const int xc = (live && base >= 0 && base + i16 < st[4]) ? st[kDagStepHead + (t * kTileM + i16) * 3] : -1;
-      xo[t] = xc <= -2 ? (uint32_t)(((-2 - xc) * H + xcol + 4 * g4) * 4) : kNoSource;
-    }
-  };
-  auto issue_x = [&](const int *st, u32x4 (&xv)[MT][NBX], bool live) __attribute__((always_inline)) {
-    uint32_t xo[MT];
-    x_offsets(st, live, xo);
-#pragma unroll
-    for (int t = 0; t < MT; ++t)
-#pragma unroll
-      for (int b = 0; b < NBX; ++b) xv[t][b] = xin.load4(xo[t] + 64u * b);
-  };
-
-  // One step.  half_c: the step's units as a compile-time constant (0: the
-  // slice's 64, 1: its first 32, 2: its last 32; a half step has one tile);
-  // xc: its input fragments (requested earlier); nst: the next step
-  // (nullptr: none), whose input fragments go to xn.  Returns true when the
-  // kernel must stop.
-  auto run_step = [&](auto half_c, const int *st, const u32x4 (&xc)[MT][NBX], const int *nst,
-                      u32x4 (&xn)[MT][NBX]) __attribute__((always_inline)) -> bool {
-    constexpr int kHalf = decltype(half_c)::value;
-    constexpr int NT0 = kHalf == 2 ? NT / 2 : 0;         // first n-tile of the step's units
-    constexpr int NTS = kHalf == 0 ? NT : NT / 2;        // n-tiles of the step's units
-    const int l = st[0], lend = st[4];
-    const bool two = kHalf == 0 && st[3] >= 0;
-    // epilogue thread: unit ej (within the slice) of row quarter eq of tile
-    // et; a whole step uses every thread, a half step the first 128
-    const int ej = kHalf == 0 ? (tid & (J - 1)) : J / 2 * (kHalf - 1) + (tid & (J / 2 - 1));
-    const int et = kHalf == 0 ? tid / (J * 4) : 0;
-    const int eq = kHalf == 0 ? (tid / J) & 3 : (tid / (J / 2)) & 3;
-    const bool elive = kHalf == 0 ? (et == 0 || two) : tid < J / 2 * 4;
-    Frag hv[MT][NBR];
-    int cr[MT];
-    uint32_t ho[MT];
-#pragma unroll
-    for (int t = 0; t < MT; ++t) {
-      const int base = st[2 + t];
-      cr[t] = (base >= 0 && base + i16 < lend) ? st[kDagStepHead + (t * kTileM + i16) * 3 + 1 + rslot] : -1;
-      ho[t] = cr[t] >= 0 ? (uint32_t)(cr[t] * H + rcol + 4 * g4) * 8u : kNoSource;
-    }
-    floatx4 acc[MT][NT];
-#pragma unroll
-    for (int t = 0; t < MT; ++t)
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) acc[t][nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-    // the accumulators and recurrent weights of the step's units
-    auto step_acc = [&](int t) __attribute__((always_inline)) -> floatx4 (&)[NTS] {
-      return *reinterpret_cast<floatx4 (*)[NTS]>(&acc[t][NT0]);
-    };
-    auto step_wr = [&](int b) __attribute__((always_inline)) -> const float4 (&)[NTS] {
-      return *reinterpret_cast<const float4 (*)[NTS]>(&wr[b][NT0]);
-    };
-    float pv[4];                             // hoisted: W x + b of the thread's four outputs
-    if constexpr (kHoisted) {
-      // 1. (hoisted) the step's input products, computed before the level
-      // loop, for the epilogue's four outputs of this thread, then every
-      // child-state fragment of the step at once: there is no input part to
-      // place them in
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int row = st[2 + et] + 4 * eq + v;
-        pv[v] = as_float(pin.load1((elive && row < lend) ? (uint32_t)(row * H + hbase + ej) * 4u : kNoSource));
-      }
-#pragma unroll
-      for (int k = 0; k < NBR; ++k) {
-        hv[0][k].lo = hs.load2_at(ho[0] + 128u * k);
-        hv[0][k].hi = hs.load2_at(ho[0] + 128u * k + 16u);
-        if (two) {
-          hv[1][k].lo = hs.load2_at(ho[1] + 128u * k);
-          hv[1][k].hi = hs.load2_at(ho[1] + 128u * k + 16u);
-        }
-      }
-    } else {
-      uint32_t xo_next[MT];
-      x_offsets(nst ? nst : st, nst != nullptr, xo_next);
-      // 1. input part; one weight fragment serves both tiles.  The next
-      // step's input fragments are requested during its first half and the
-      // child-state fragments of tile 0's rows during its second half, one
-      // load or one block per MFMA step, rather than in bursts,
-      // which would hold the MFMAs behind them until the address unit has
-      // taken every load.  The child fragments are not requested at the
-      // start: a level's children are written at the end of the previous
-      // level, about when this step begins, so pairs read at once would
-      // mostly still carry old tags.
-      const float *bx = &Wx_s[i16 * LDX + xcol + 4 * g4];
-#pragma unroll
-      for (int b = 0; b < NBX; ++b) {
-        float4 wv[NTS];
-#pragma unroll
-        for (int nt = 0; nt < NTS; ++nt) wv[nt] = *(const float4 *)(bx + (NT0 + nt) * 16 * LDX + 16 * b);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          mfma_kstep_xn<NTS>(k, as_float4(xc[0][b]), wv, step_acc(0));
-          if (two) mfma_kstep_xn<NTS>(k, as_float4(xc[1][b]), wv, step_acc(1));
-          if (b == 0) {
-            static_assert(MT * NBX == 4, "one next-step input load per MFMA step");
-            xn[k / NBX][k % NBX] = xin.load4(xo_next[k / NBX] + 64u * (k % NBX));
-          }
-          if (b == NBX - 1) {
-            // (tile 1's blocks follow during tile 0's recurrent part)
-            static_assert(NBR == 4, "one child block per MFMA step");
-            hv[0][k].lo = hs.load2_at(ho[0] + 128u * k);
-            hv[0][k].hi = hs.load2_at(ho[0] + 128u * k + 16u);
-          }
-        }
-      }
-    }
-    CORTEX_TRACE_POINT(l, 1);
-    // 2. per tile: wait until its child fragments carry the launch tag, then
-    // contract them.  With the fused input part, tile 1's fragments are
-    // requested between the MFMA blocks of tile 0's contraction, so the
-    // address unit takes half the fragments during the input part and half
-    // in the shadow of tile 0's recurrent MFMAs.
-    auto wait_tile = [&](int t) __attribute__((always_inline)) {
-      auto ready_t = [&]() __attribute__((always_inline)) -> bool {
-        bool rt = true;
-#pragma unroll
-        for (int b = 0; b < NBR; ++b) rt = rt && hv[t][b].ready(tag);
-        return cr[t] < 0 || rt;
-      };
-      if (gave_up || ready_t()) return;
-      const uint64_t t0 = wall_clock64();
-      for (;;) {
-        __builtin_amdgcn_s_sleep(1);
-#pragma unroll
-        for (int b = 0; b < NBR; ++b)
-          if (cr[t] >= 0 && !hv[t][b].ready(tag)) {
-            hv[t][b].lo = hs.load2_at(ho[t] + 128u * b);
-            hv[t][b].hi = hs.load2_at(ho[t] + 128u * b + 16u);
-          }
-        // the status first: a load still in flight at the exit would hold
-        // back the MFMAs that follow until it returns
-        if (load_status(a.status) != 0) {
-          gave_up = 1;
-          break;
-        }
-        if (ready_t()) break;
-        if (wall_clock64() - t0 > a.timeout) {
-          raise_status(a.status, CORTEX_ST_BARRIER_TIMEOUT);
-          gave_up = 1;
-          break;
-        }
-      }
-      if (gave_up) stop_s = 1;             // read by every wave after the next barrier
-    };
-    wait_tile(0);
-    CORTEX_TRACE_POINT(l, 2);
-    // 3. recurrent part
-#pragma unroll
-    for (int b = 0; b < NBR; ++b) {
-      mfma_k16_xn<NTS>(hv[0][b].value(true), step_wr(b), step_acc(0));
-      if (!kHoisted && two) {
-        hv[1][b].lo = hs.load2_at(ho[1] + 128u * b);
-        hv[1][b].hi = hs.load2_at(ho[1] + 128u * b + 16u);
-      }
-    }
-    if (two) {
-      wait_tile(1);
-#pragma unroll
-      for (int b = 0; b < NBR; ++b) mfma_k16_xn<NTS>(hv[1][b].value(true), step_wr(b), step_acc(1));
-    }
-    CORTEX_TRACE_WAVE(l);
-    // the next step's input fragments are complete before this step's stores
-    // are issued, so its first contraction does not wait for the stores
-    if constexpr (!kHoisted)
-#pragma unroll
-      for (int t = 0; t < MT; ++t)
-#pragma unroll
-        for (int b = 0; b < NBX; ++b) settle(xn[t][b]);
-#pragma unroll
-    for (int t = 0; t < MT; ++t)
-      if (t == 0 || two)
-#pragma unroll
-        for (int nt = NT0; nt < NT0 + NTS; ++nt) {
-          const int c = nt * 16 + i16;
-          *(floatx4 *)&C_s[((wave * MT + t) * J + c) * kTileM + 4 * (g4 ^ ((c >> 2) & 3))] = acc[t][nt];
-        }
-    __syncthreads();
-    CORTEX_TRACE_POINT(l, 3);
-    if (stop_s) return true;               // a wave gave up its wait: every wave stops here
-    // epilogue: thread (unit ej, row quarter eq of tile et) sums the eight
-    // partial sums of four rows, bias first, and writes them; every output of
-    // the thread first, then the stores (a store's data registers are not
-    // reused while earlier stores are in flight)
-    static_assert(EPI == 4 && kFwdThreads == J * MT * 4, "one row quarter of one tile per thread");
-    floatx4 sum = kHoisted ? floatx4{pv[0], pv[1], pv[2], pv[3]} : floatx4{bias_s[ej], bias_s[ej], bias_s[ej], bias_s[ej]};
-    if (elive) {
-#pragma unroll
-      for (int w = 0; w < kFwdWaves; ++w) {
-        const floatx4 p = *(const floatx4 *)&C_s[((w * MT + et) * J + ej) * kTileM + 4 * (eq ^ ((ej >> 2) & 3))];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) sum[v] += p[v];
-      }
-    }
-    // C_s is written again by the next step: every wave has read it once all
-    // pass here, before the tanh and the stores, so the stores hold nobody up
-    __syncthreads();
-    float hv_out[EPI];
-    uint32_t el[EPI];
-#pragma unroll
-    for (int v = 0; v < EPI; ++v) {
-      const int row = st[2 + et] + 4 * eq + v;
-      hv_out[v] = tanh_f(sum[v]);
-      el[v] = (elive && row < lend) ? (uint32_t)(row * H + hbase + ej) : 0xFFFFFFFFu;
-    }
-    // the tagged pairs (what the next level waits for) first, then the outputs
-#pragma unroll
-    for (int v = 0; v < EPI; ++v)
-      if (el[v] != 0xFFFFFFFFu) hs.store1(el[v], hv_out[v], tag);
-#pragma unroll
-    for (int v = 0; v < EPI; ++v)
-      if (el[v] != 0xFFFFFFFFu) a.h[el[v]] = hv_out[v];
-    CORTEX_TRACE_POINT(l, 4);
-    return false;
-  };
-
-  u32x4 xa[MT][NBX], xb[MT][NBX];
-  // one flat pass over this group's steps, level after level, a listed chunk
-  // at a time
-  auto step = [&](int e) __attribute__((always_inline)) -> const int * { return &list[e * SI]; };
-  for (int first = 0;;) {
-    // two steps per iteration, written out, so each step's input fragments
-    // stay in fixed registers (xa, xb) rather than being selected at run time
-    if (!kHoisted && listed > 0) {
-      issue_x(step(0), xa, true);
-#pragma unroll
-      for (int t = 0; t < MT; ++t)
-#pragma unroll
-        for (int b = 0; b < NBX; ++b) settle(xa[t][b]);
-    }
-    // Steps of one kind (whole or half) run in a loop of their own, entered
-    // with no load in flight: a loop entered with another kind's loads
-    // pending would wait for them on every iteration, since the compiler's
-    // wait counts merge every path into the loop.
-    int e = 0;
-    auto run_kind = [&](auto half_c) __attribute__((always_inline)) -> bool {
-      constexpr int kKind = decltype(half_c)::value;
-      for (;;) {
-        CORTEX_TRACE_POINT(step(e)[0], 0);
-        if (run_step(half_c, step(e), xa, e + 1 < listed ? step(e + 1) : nullptr, xb)) return true;
-        CORTEX_TRACE_POINT(step(e)[0], 5);
-        if (++e >= listed) return false;
-        if (step(e)[5] != kKind) {
-          // the next step's input fragments are in xb; the next run reads xa
-#pragma unroll
-          for (int t = 0; t < MT; ++t)
-#pragma unroll
-            for (int b = 0; b < NBX; ++b) xa[t][b] = xb[t][b];
-          return false;
-        }
-        CORTEX_TRACE_POINT(step(e)[0], 0);
-        if (run_step(half_c, step(e), xb, e + 1 < listed ? step(e + 1) : nullptr, xa)) return true;
-        CORTEX_TRACE_POINT(step(e)[0], 5);
-        if (++e >= listed || step(e)[5] != kKind) return false;
-      }
-    };
-    while (e < listed) {
-      __builtin_amdgcn_s_waitcnt(kWaitVmcntZero);
-      const int kind = step(e)[5];
-      const bool stop = kind == 1   ? run_kind(std::integral_constant<int, 1>{})
-                        : kind == 2 ? run_kind(std::integral_constant<int, 2>{})
-                                    : run_kind(std::integral_constant<int, 0>{});
-      if (stop) return;
-    }
-    first += kDagStepCap;
-    if (first >= total) break;
-    // the next chunk: every wave is done with this one's records
-    __syncthreads();
-    int bad_chunk = 0;
-    list_steps(first, bad_chunk);
-    listed = min(total - first, kDagStepCap);
-    __syncthreads();                           // the step records are written
-    int crow[kFillPer], cv[kFillPer], c0[kFillPer], c1[kFillPer];
-#pragma unroll
-    for (int k = 0; k < kFillPer; ++k) {
-      const int idx = tid + k * kFwdThreads;
-      crow[k] = idx < listed * kDagStepRows ? dag_slot_row(&list[(idx / kDagStepRows) * SI], idx % kDagStepRows) : -1;
-      cv[k] = c0[k] = c1[k] = -1;
-      if (crow[k] >= 0) {
-        cv[k] = a.level_nodes[crow[k]];
-        c0[k] = a.child_rows[(size_t)crow[k] * 2];
-        c1[k] = a.child_rows[(size_t)crow[k] * 2 + 1];
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < kFillPer; ++k) {
-      const int idx = tid + k * kFwdThreads;
-      if (idx < listed * kDagStepRows &&
-          !dag_store_codes(a, &list[(idx / kDagStepRows) * SI], idx % kDagStepRows, crow[k] >= 0, cv[k], c0[k], c1[k]))
-        bad_chunk = 1;
-    }
-    if (__syncthreads_or(bad_chunk)) {
-      raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
-      return;
-    }
-  }
-  CORTEX_TRACE_KERNEL(3);
-  if (a.retire) retire_tag(a.sync, tag, a.status, a.timeout);
 }
 
 // ---------------------------------------------------------------------------
@@ -3261,15 +2706,16 @@ static void pick_slice(bool cached, Instance &out) {
 template <int CELL, int H, int J>
 static bool pick_split(Instance &out, int32_t N, bool fused = false) {
   using D = SplitDims<CELL, H, J>;
+  constexpr bool kAblate = !(CELL == CELL_DAG && J > 16);       // has the instance without model persistence
   out.J = J;
   out.threads = kFwdThreads;
   out.level_barrier_ok = out.level_range_ok = true;
   out.ablate_bits = SrcCfg<CELL>::kLeafX ? 3 : 1;
-  if (D::kDag && fused) {
-    out.fn = slice_split_kernel<CELL, H, J, D::kDag>;
+  if (D::kDag && kAblate && fused) {
+    out.fn = slice_split_kernel<CELL, H, J, D::kDag && kAblate>;
     out.lds = split_list_bytes<D::CODES>(kSplitFusedCap) + (N + small_lin_ints<kFwdThreads>(N, 2)) * sizeof(int);
   } else {
-    out.fn = (knob(CORTEX_KNOB_ABLATE) & 1) ? slice_split_kernel<CELL, H, J, false, true> : slice_split_kernel<CELL, H, J, false>;
+    out.fn = (knob(CORTEX_KNOB_ABLATE) & 1) ? slice_split_kernel<CELL, H, J, false, kAblate> : slice_split_kernel<CELL, H, J, false>;
     out.lds = split_list_bytes<D::CODES>(kSplitCap);
   }
   return true;
@@ -3337,18 +2783,25 @@ static bool pick(int cell, int H, int32_t N, int32_t K, bool cached, Instance &o
       return true;
     }
   }
-  // DAG-RNN at H = 256: four 64-unit slices for large batches (operand
-  // re-reads dominate there), sixteen 16-unit slices for small ones (a
-  // tile's contraction is 4x shorter, and small levels are latency-bound);
-  // the knob forces either (16 or 64)
+  // DAG-RNN at H = 256: 32- or 64-unit slices for large batches (operand
+  // re-reads and tiles per group dominate there), sixteen 16-unit slices for
+  // small ones (a tile's contraction is shorter, and small levels are
+  // latency-bound); the knob forces 16 or 64.  us per step (16 / 32 / 64 units),
+  // grids of 32x32: 6 grids 249 / 257 / 280, 12: 284 / 265 / 288, 20: 320 / 287 /
+  // 303, 32: 402 / 327 / 333, 48: 537 / 377 / 360, 64: 672 / 434 / 385, 250:
+  // 2,490 / - / 938; 10x10: 40 grids 109 / 109 / 120, 64: 123 / 115 / 126
   if (cell == CELL_DAG && H == kDagH && (units == 64 || (units != 16 && N >= kDagWideMinRows))) {
-    // ablation bit 2: the input products hoisted into dag_input_gemm_kernel
-    out.fn = (knob(CORTEX_KNOB_ABLATE) & 4) ? dag_slice64_kernel<true> : dag_slice64_kernel<false>;
+    const bool hoisted = knob(CORTEX_KNOB_ABLATE) & 4;       // the input products in dag_input_gemm_kernel
+    if (hoisted || units == 64 || N >= kDag64MinRows) {
+      pick_split<CELL_DAG, kDagH, kDagJ>(out, N);
+      out.fn = hoisted ? slice_split_kernel<CELL_DAG, kDagH, kDagJ, false, false, true>
+                       : slice_split_kernel<CELL_DAG, kDagH, kDagJ, false>;
+    } else {
+      pick_split<CELL_DAG, kDagH, 32>(out, N);
+      out.fn = slice_split_kernel<CELL_DAG, kDagH, 32, false>;
+    }
+    out.level_barrier_ok = false;
     out.ablate_bits = 4;
-    out.J = kDagJ;
-    out.threads = kFwdThreads;
-    out.lds = kDagListBytes;
-    out.level_range_ok = true;
     return true;
   }
   if (pick_slice_split(cell, H, N, K, units, false, out)) return true;

@@ -212,18 +212,24 @@ __device__ __forceinline__ int list_tiles(const Off &off, int L, int N, int lo, 
 // slices of a group then share their XCD's L2, and a stale line only shows an
 // old tag, after which the polls are device-scope.
 // ---------------------------------------------------------------------------
-template <int CELL, int H, int J_>
+template <int CELL, int H, int J_, bool kHoisted = false>
 struct SplitDims {
   static constexpr int J = J_, GATES = Cell<CELL, H>::GATES, GJ = GATES * J, NT = (GJ + 15) / 16;
   static constexpr bool kDag = CELL == CELL_DAG;
   static constexpr int CODES = SrcCfg<CELL>::SEGS;
-  static constexpr int KX = kDag ? H / 8 : 0, XS = KX / 32;          // input columns per wave, 32-column steps
+  static constexpr int KX = kDag && !kHoisted ? H / 8 : 0, XS = KX / 32;          // input columns per wave, 32-column steps
   static constexpr int KR = 2 * H / 8, RS = KR / 32;                  // recurrent columns per wave
   // row stride of the partial sums: 4 rows apart is 16 banks apart, so neither
   // the MFMA-layout writes nor the unit-major reads conflict
   static constexpr int LDC = 16 * NT + 4;
   static constexpr int kPairs = kTileM * J;                           // (row, unit) pairs of a tile
-  static constexpr int PP = kPairs > 256 ? kPairs / 256 : 1;          // pairs per epilogue thread
+  // DAG-RNN with 64 units: the input weights' planes sit in LDS (96 KB: in
+  // registers they spill, 64 grids 570 against 385 us), so there is one buffer of
+  // partial sums, and every thread takes part in the epilogue
+  static constexpr bool kWxLds = XS > 0 && J == 64;
+  static constexpr int ET = kDag && J == 64 ? 512 : 256;                       // epilogue threads
+  static constexpr int PP = kPairs > ET ? kPairs / ET : 1;            // pairs per epilogue thread
+  static constexpr int RSTEP = J == 64 ? ET / 64 : 4;                 // rows between a thread's pairs
   static constexpr int PARTS = kPairs < 256 ? 256 / kPairs : 1;       // threads per pair
   static_assert(KR % 32 == 0 && (!kDag || KX % 32 == 0) && 4 * KR == H, "whole 32-column steps, one child slot per wave");
   static_assert(PARTS <= 8 && H % J == 0 && J <= 64, "epilogue mapping");
@@ -235,9 +241,11 @@ template <int CODES>
 constexpr size_t split_list_bytes(int cap) { return (size_t)cap * TileList<CODES>::kInts * sizeof(int); }
 constexpr int kSplitCap = 128, kSplitFusedCap = 48;
 
-template <int CELL, int H, int J, bool kFused, bool kWeightsFromMemory = false>
+// kHoisted (ablation, DAG-RNN with 64 units): W x + b of every row is read from
+// a.pre instead of being contracted here.
+template <int CELL, int H, int J, bool kFused, bool kWeightsFromMemory = false, bool kHoisted = false>
 __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
-  using D = SplitDims<CELL, H, J>;
+  using D = SplitDims<CELL, H, J, kHoisted>;
   using TL = TileList<D::CODES>;
   constexpr int NT = D::NT, XS = D::XS, RS = D::RS, GATES = D::GATES, LDC = D::LDC, PP = D::PP, PARTS = D::PARTS;
   constexpr int INTS = TL::kInts, HEAD = TL::kHead, CODES = D::CODES;
@@ -245,7 +253,10 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
   constexpr int kCap = kFused ? kSplitFusedCap : kSplitCap;
   constexpr int CBUF = kFwdWaves * kTileM * LDC;
 
-  __shared__ __attribute__((aligned(16))) float C_s[2 * CBUF];
+  constexpr bool kWxLds = D::kWxLds, kOneBuffer = D::ET == 512;
+  constexpr int WXP = XS * NT * kFwdThreads;    // one plane of the input weights, [step][tile][thread]
+  __shared__ __attribute__((aligned(16))) float C_s[(kOneBuffer ? 1 : 2) * CBUF];
+  __shared__ u32x4 Wx_s[kWxLds ? 3 * WXP : 1];
   __shared__ int wsum[kFwdWaves + 1];
   __shared__ int stop_s[2];
   extern __shared__ int dyn[];
@@ -260,10 +271,11 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
   const TagBuf cs(a.cs, kLstm ? (uint32_t)N * H * 8 : 0u);
   const InBuf xin(kDag ? (const void *)a.x : (const void *)a.x_table,
                   kDag ? (uint32_t)N * H * 4 : (a.x_table ? (uint32_t)a.x_rows * H * 4 : 0u));
+  const InBuf pin(a.pre, kHoisted ? (uint32_t)N * H * 4 : 0u);
   const int rslot = wave >> 2, rcol = D::KR * (wave & 3) + 4 * g4;    // child slot; lane's first column in it
   const int xcol = D::KX * wave + 4 * g4;
   // epilogue: unit ej, part epart of the eight partial sums, rows erow + 4 p
-  const int et = tid & 255, eside = tid >> 8;
+  const int et = tid & (D::ET - 1), eside = kOneBuffer ? 0 : tid >> 8;
   const int ej = et % J, epart = J >= 16 ? 0 : (et & 15) / J;
   const int erow = J == 64 ? et >> 6 : (J == 32 ? 8 * ((et >> 5) & 1) + (et >> 6) : 4 * ((et >> 4) & 3) + (et >> 6));
 
@@ -282,7 +294,8 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
     return weight_slice_at<CELL, H, J>(a, hbase, 16 * nt + row, wcol(s, half));
   };
   constexpr int WS = kWeightsFromMemory ? 1 : XS + RS;
-  Split8 w[WS][NT];
+  constexpr int W0 = kWxLds ? XS : 0;           // steps whose weights are in LDS
+  Split8 w[WS - W0][NT];
   float wmax = 0.f;
   float bias[GATES];
 #pragma unroll
@@ -293,7 +306,16 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
         wmax = max_abs(max_abs(wmax, v[s][nt][0]), v[s][nt][1]);
-        w[s][nt] = split8(v[s][nt][0], v[s][nt][1]);
+        const Split8 p = split8(v[s][nt][0], v[s][nt][1]);
+        if (s < W0) {
+          // (each lane reads back only what it wrote: no barrier)
+          u32x4 *o = &Wx_s[(s * NT + nt) * kFwdThreads + tid];
+          o[0] = __builtin_bit_cast(u32x4, p.p0);
+          o[WXP] = __builtin_bit_cast(u32x4, p.p1);
+          o[2 * WXP] = __builtin_bit_cast(u32x4, p.p2);
+        } else {
+          w[s - W0 < 0 ? 0 : s - W0][nt] = p;
+        }
       }
   };
 
@@ -506,7 +528,7 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
   auto fp32_sum = [&](const int *t, int i, int gate_row) __attribute__((always_inline)) -> float {
     float sum = 0.f;
 #pragma unroll 1
-    for (int c = 0; c < CODES * H; c += 4) {
+    for (int c = kHoisted ? H : 0; c < CODES * H; c += 4) {
       const int src = code(t, i, c / H), o = c % H;
       float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
       if (src >= 0) {
@@ -557,7 +579,7 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
     if (listed > 0) {
       cd = code(list, i16, kDag ? 1 + rslot : rslot);
       static_for<kLoads>([&](auto k) __attribute__((always_inline)) { issue_load(staged_off(cd), plain_off(cd), k); });
-      if (kDag) issue_x(code(list, i16, 0));
+      if (XS > 0) issue_x(code(list, i16, 0));
       issue_cells(list, 0);
     }
     if (kLeafInputs && first == 0 && a.level_lo == 0) {
@@ -575,6 +597,35 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
         write_leaf_outputs<H, kLstm>(a, nullptr, off1, hs, cs, tag);
       }
     }
+    // a tile's accumulators, and the largest operand met
+    floatx4 hi[NT], lo[NT];
+    float mx = wmax;
+    // 32 columns of step s: v0, v1 are this lane's four columns of its two blocks
+    auto contract = [&](auto s, const float4 v0, const float4 v1, auto between) __attribute__((always_inline)) {
+      if constexpr (kWeightsFromMemory) {
+        Split8 wm[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const float4 w0 = wfrag(s, nt, 0, i16), w1 = wfrag(s, nt, 1, i16);
+          mx = max_abs(max_abs(mx, w0), w1);
+          wm[nt] = split8(w0, w1);
+        }
+        mfma_split<NT>(split8(v0, v1), wm, hi, lo, between);
+      } else {
+        if constexpr (s < W0) {
+          Split8 wm[NT];
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) {
+            const u32x4 *o = &Wx_s[(s * NT + nt) * kFwdThreads + tid];
+            wm[nt] = Split8{__builtin_bit_cast(bf16x8, o[0]), __builtin_bit_cast(bf16x8, o[WXP]),
+                            __builtin_bit_cast(bf16x8, o[2 * WXP])};
+          }
+          mfma_split<NT>(split8(v0, v1), wm, hi, lo, between);
+        } else {
+          mfma_split<NT>(split8(v0, v1), w[s - W0], hi, lo, between);
+        }
+      }
+    };
     for (int e = 0; e < listed; ++e) {
       const int *t = &list[e * INTS], *tn = &list[(e + 1 < listed ? e + 1 : e) * INTS];
       const bool more = e + 1 < listed;
@@ -584,32 +635,25 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
           if (!grid_sync<false>(SyncWords{a.sync}, a.status, a.timeout)) return;
       }
       CORTEX_TRACE_POINT(l, 0);
-      floatx4 hi[NT], lo[NT];
+      // the part that waits for nothing
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) hi[nt] = lo[nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-      float mx = wmax;
-      // 32 columns of step s: v0, v1 are this lane's four columns of its two blocks
-      auto contract = [&](auto s, const float4 v0, const float4 v1, auto between) __attribute__((always_inline)) {
-        if constexpr (kWeightsFromMemory) {
-          Split8 wm[NT];
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) {
-            const float4 w0 = wfrag(s, nt, 0, i16), w1 = wfrag(s, nt, 1, i16);
-            mx = max_abs(max_abs(mx, w0), w1);
-            wm[nt] = split8(w0, w1);
-          }
-          mfma_split<NT>(split8(v0, v1), wm, hi, lo, between);
-        } else {
-          mfma_split<NT>(split8(v0, v1), w[s], hi, lo, between);
-        }
-      };
-      if constexpr (kDag) {
+      mx = wmax;
+      if constexpr (XS > 0) {
 #pragma unroll
         for (int b = 0; b < 2 * XS; ++b) mx = max_abs(mx, as_float4(xv[b]));
         static_for<XS>([&](auto s) __attribute__((always_inline)) {
           contract(s, as_float4(xv[2 * s]), as_float4(xv[2 * s + 1]), [](auto) {});
         });
         issue_x(more ? code(tn, i16, 0) : -1);
+      }
+      float pv[PP];                            // hoisted: W x + b of this thread's outputs
+      if constexpr (kHoisted) {
+#pragma unroll
+        for (int p = 0; p < PP; ++p) {
+          const int row = t[0] + erow + D::RSTEP * p;
+          pv[p] = as_float(pin.load1(row < t[1] ? (uint32_t)(row * H + hbase + ej) * 4u : kNoSource));
+        }
       }
       CORTEX_TRACE_POINT(l, 1);
       if (!gave_up && !ready(e)) {
@@ -650,7 +694,8 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
         // registers whose values the step took
         static_for<RS>([&](auto s) __attribute__((always_inline)) {
           const float4 v0 = block_value(std::integral_constant<int, 2 * s>{}), v1 = block_value(std::integral_constant<int, 2 * s + 1>{});
-          mx = max_abs(max_abs(mx, v0), v1);
+          // (DAG-RNN: every staged value is a tanh)
+          if constexpr (kLeafInputs) mx = max_abs(max_abs(mx, v0), v1);
           contract(std::integral_constant<int, XS + s>{}, v0, v1, [&](auto i) __attribute__((always_inline)) {
             // this step's loads, spread over its six products
             constexpr int PER = kLoads / RS, first = PER * s + PER * i / 6, last = PER * s + PER * (i + 1) / 6;
@@ -663,7 +708,7 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
         if (mx >= kSplitLimit) list[e * INTS + 3] = -1;     // read after the tile's barrier
       }
       CORTEX_TRACE_WAVE(l);
-      float *cb = &C_s[(e & 1) * CBUF];
+      float *cb = &C_s[kOneBuffer ? 0 : (e & 1) * CBUF];
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -671,14 +716,14 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
       __syncthreads();
       CORTEX_TRACE_POINT(l, 3);
       if (stop_s[e & 1]) return;             // a wave gave up its wait: every wave stops here
-      if (eside == (e & 1)) {
+      if (kOneBuffer || eside == (e & 1)) {
         // the eight partial sums in one order whatever J is, then the bias
         float z[PP][GATES];
 #pragma unroll
         for (int p = 0; p < PP; ++p)
 #pragma unroll
           for (int g = 0; g < GATES; ++g) {
-            const float *c0 = &cb[(erow + 4 * p) * LDC + g * J + ej];
+            const float *c0 = &cb[(erow + D::RSTEP * p) * LDC + g * J + ej];
             float q[kFwdWaves];
 #pragma unroll
             for (int k = 0; k < kFwdWaves / PARTS; ++k) q[k] = c0[(epart * (kFwdWaves / PARTS) + k) * kTileM * LDC];
@@ -688,14 +733,15 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
               for (int k = 0; k < n / 2; ++k) q[k] = q[2 * k] + q[2 * k + 1];
 #pragma unroll
             for (int x = 1; x < PARTS; x *= 2) q[0] += __shfl_xor(q[0], J * x);
-            z[p][g] = bias[g] + q[0];
+            z[p][g] = (kHoisted ? pv[p] : bias[g]) + q[0];
           }
+        if constexpr (kOneBuffer) __syncthreads();     // the partial sums may be overwritten
         if (__builtin_expect(t[3] < 0, 0)) {
           // an operand or a weight cannot be split: the sums in plain fp32
 #pragma unroll
           for (int p = 0; p < PP; ++p)
 #pragma unroll
-            for (int g = 0; g < GATES; ++g) z[p][g] = bias[g] + fp32_sum(t, erow + 4 * p, g * J + ej);
+            for (int g = 0; g < GATES; ++g) z[p][g] = (kHoisted ? pv[p] : bias[g]) + fp32_sum(t, erow + D::RSTEP * p, g * J + ej);
         }
         if constexpr (kLstm) {
           const int row = t[0] + erow;
@@ -716,12 +762,12 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
           // the tagged pairs (what the next level waits for) first, then the outputs
 #pragma unroll
           for (int p = 0; p < PP; ++p) {
-            const int row = t[0] + erow + 4 * p;
+            const int row = t[0] + erow + D::RSTEP * p;
             if (epart == 0 && row < t[1]) hs.store1((uint32_t)(row * H + hbase + ej), hv[p], tag);
           }
 #pragma unroll
           for (int p = 0; p < PP; ++p) {
-            const int row = t[0] + erow + 4 * p;
+            const int row = t[0] + erow + D::RSTEP * p;
             if (epart == 0 && row < t[1]) a.h[(size_t)row * H + hbase + ej] = hv[p];
           }
         }

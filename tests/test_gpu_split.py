@@ -58,6 +58,10 @@ SIZES = {
     "childsum_h256_all_leaves": lambda: childsum(16, 1201, 1, 1),
     "childsum_h256_forest": lambda: childsum(17, 333, 1, 60),
     "dag_h256_1x1": lambda: I.dagrnn_workload(10, n_grids=1, rows=1, cols=1, H=256),
+    "dag_h256_6143": lambda: I.dagrnn_workload(25, n_grids=1, rows=1, cols=6143, H=256),
+    "dag_h256_6144": lambda: I.dagrnn_workload(26, n_grids=2, rows=48, cols=64, H=256),
+    "dag_h256_36863": lambda: I.dagrnn_workload(27, n_grids=191, rows=1, cols=193, H=256),
+    "dag_h256_36865": lambda: I.dagrnn_workload(28, n_grids=365, rows=1, cols=101, H=256),
     "dag_h512_33x17": lambda: I.dagrnn_workload(11, n_grids=5, rows=33, cols=17, H=512),
 }
 
