@@ -126,6 +126,9 @@ struct TagBuf {
   __device__ __forceinline__ u32x4 first2_at(uint32_t off) const {
     return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
   }
+  __device__ __forceinline__ u32x2 first1_at(uint32_t off) const {
+    return __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+  }
   __device__ __forceinline__ u32x2 load1_at(uint32_t off) const {
     return __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, kScopeDevice);
   }

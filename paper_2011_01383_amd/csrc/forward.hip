@@ -95,7 +95,8 @@ struct FwdArgs {
   int32_t level_lo, level_hi;   // levels this launch runs (all of them unless one launch per level)
   int32_t level_barrier;        // 1: a device-wide barrier closes every level (instead of per-datum waits alone);
                                 // 2 (TreeGRU): also one between the level's two exchanges
-  float *keep;                  // TreeGRU, level_barrier 2: z, W_h x + b_h and h~ per (row, unit), [3][N][H]
+  float *keep;                  // MV-RNN at d = 128: tagged partial sums of [B a; A b], [N][8][2 d];
+                                // TreeGRU, level_barrier 2: z, W_h x + b_h and h~ per (row, unit), [3][N][H]
   // fused launch (cortex_tree_infer): the children to linearize, and where
   // workgroup 0 writes the linearization
   const int32_t *children;
@@ -2333,7 +2334,7 @@ __device__ __forceinline__ bool level_bounds(const FwdArgs &a, int l, int &r0, i
 }
 
 // ---------------------------------------------------------------------------
-// MV-RNN (d = 64 or 128): p = tanh(W [B a; A b]), P = W_M [A; B].
+// MV-RNN (d = 64): p = tanh(W [B a; A b]), P = W_M [A; B].
 // Node-parallel: with RB = d / 16 row blocks and G/RB node groups, workgroup
 // b owns output rows [16 r, 16 r + 16), r = b / (G/RB), of every node it
 // processes (its 16 rows of W_M in LDS, its share of the same rows of W in
@@ -2357,12 +2358,10 @@ struct MvDims {
   static constexpr int kGroups = 2 * D * D / 4 / kThreads;   // float4 groups of [A;B] per thread
   static constexpr int kSide = D * D / 4;                // float4 groups per matrix
   static constexpr int kParts = kThreads / 16;           // partial sums per output of p (8 terms each)
-  // the cache (3 ints per row) must fit beside the static LDS: 36 KB at
-  // d = 64, 7.5 KB at d = 128 (where [A;B] alone takes 129 KB)
-  static constexpr int kCacheRows = D == 64 ? 3072 : 640;
+  static constexpr int kCacheRows = 3072;                // 3 ints per row beside the static LDS
   static_assert(kParts * 8 == 2 * D && kGroups * kThreads * 4 == 2 * D * D, "MV-RNN tiling");
 };
-constexpr int kMvD = 64, kMvD2 = 128;
+constexpr int kMvD = 64;
 
 // Fused launches (cortex_tree_infer): the batch is linearized in LDS first.
 // Dynamic LDS (ints): child rows (2N), leaf input rows (N), level offsets
@@ -2672,6 +2671,7 @@ struct Instance {
   bool level_range_ok = false;     // honours FwdArgs.level_lo / level_hi
   bool phase_barrier_ok = false;   // has two exchanges per level and honours level_barrier 2
   bool one_group = false;          // the whole batch in one workgroup
+  bool uses_keep = false;          // needs the region behind the second staging (FwdArgs.keep)
   int ablate_bits = 0;             // FwdArgs.ablate bits the kernel honours
 };
 
@@ -2855,11 +2855,12 @@ static bool pick(int cell, int H, int32_t N, int32_t K, bool cached, Instance &o
     out.lds = N <= MvDims<kMvD>::kCacheRows ? 3 * (size_t)N * sizeof(int) : 0;
     return true;
   }
-  if (cell == CORTEX_MVRNN && H == kMvD2) {
-    out.fn = mvrnn_forward_kernel<kMvD2, false>;
-    out.J = MvDims<kMvD2>::RB;
-    out.threads = MvDims<kMvD2>::kThreads;
-    out.lds = N <= MvDims<kMvD2>::kCacheRows ? 3 * (size_t)N * sizeof(int) : 0;
+  if (cell == CORTEX_MVRNN && H == MvCols::D) {
+    out.fn = mvrnn_cols_kernel;
+    out.J = MvCols::RB;
+    out.threads = kFwdThreads;
+    out.lds = 0;
+    out.uses_keep = true;
     return true;
   }
   return false;
@@ -2905,11 +2906,11 @@ static bool pick_fused(int cell, int H, int32_t N, int32_t K, Instance &out) {
     if ((units != 0 && units != 16) || (H == 256 && units == 0 && N >= kDagWideMinRows)) return false;
     return pick_slice_split(cell, H, N, K, units, true, out);
   }
-  if (cell == CORTEX_MVRNN && (H == kMvD || H == kMvD2) && K == 2) {
-    out.fn = H == kMvD ? mvrnn_forward_kernel<kMvD, true> : mvrnn_forward_kernel<kMvD2, true>;
-    out.J = H == kMvD ? MvDims<kMvD>::RB : MvDims<kMvD2>::RB;
-    out.threads = H == kMvD ? MvDims<kMvD>::kThreads : MvDims<kMvD2>::kThreads;
-    out.lds = (H == kMvD ? mv_fused_ints<kMvD>(N) : mv_fused_ints<kMvD2>(N)) * sizeof(int);
+  if (cell == CORTEX_MVRNN && H == kMvD && K == 2) {
+    out.fn = mvrnn_forward_kernel<kMvD, true>;
+    out.J = MvDims<kMvD>::RB;
+    out.threads = MvDims<kMvD>::kThreads;
+    out.lds = mv_fused_ints<kMvD>(N) * sizeof(int);
     return true;
   }
   const bool gru = cell == CORTEX_CHILDSUM_TREEGRU || cell == CORTEX_SIMPLE_TREEGRU;
@@ -2950,8 +2951,12 @@ static int staged_tensors(int32_t cell) {
 // bytes of the second staged tensor: c [N, H], P [N, H, H] for MV-RNN, or the
 // TreeGRU reset sums m [N, H] followed by the kept phase-A values [3, N, H]
 static size_t keep_bytes(int32_t N, int32_t H) { return align_up((size_t)N * H * 3 * sizeof(float), 256); }
+// MV-RNN at d = 128: the published partial sums of [B a; A b], tagged pairs
+static size_t mv_exchange_bytes(int32_t N, int32_t H) {
+  return H == MvCols::D ? align_up((size_t)N * MvCols::kXchg * 8, 256) : 0;
+}
 static size_t second_staging_bytes(int32_t cell, int32_t N, int32_t H) {
-  if (cell == CORTEX_MVRNN) return align_up((size_t)N * H * H * 8, 256);
+  if (cell == CORTEX_MVRNN) return align_up((size_t)N * H * H * 8, 256) + mv_exchange_bytes(N, H);
   if (cell == CORTEX_CHILDSUM_TREEGRU || cell == CORTEX_SIMPLE_TREEGRU) return staging_bytes(N, H) + keep_bytes(N, H);
   return staging_bytes(N, H);
 }
@@ -3042,7 +3047,7 @@ static int launch_forward(int cell, int H, const cortex_lin_t *lin, FwdArgs &a, 
   a.timeout = barrier_timeout_ticks();
   a.hs = reg.hs;
   a.cs = reg.cs;                                     // c, P for MV-RNN, or the TreeGRU reset sums
-  a.keep = inst.phase_barrier_ok ? reg.keep : nullptr;
+  a.keep = inst.phase_barrier_ok || inst.uses_keep ? reg.keep : nullptr;
   a.retire = 1;                 // the tag itself comes from the workspace header (launch_tag)
   a.level_lo = 0;
   a.level_hi = 0x7fffffff;
@@ -3215,7 +3220,9 @@ bool fixed_regions(int32_t cell, int32_t N, int32_t H, void *header, size_t head
   const int staged = staged_tensors(cell);
   const size_t need_hs = staged >= 1 ? cs_off - hs_off : 0;
   const size_t need_cs = staged >= 2 ? keep_off - cs_off : 0;
-  const size_t need_keep = (cell == CORTEX_CHILDSUM_TREEGRU || cell == CORTEX_SIMPLE_TREEGRU) ? keep_bytes(N, H) : 0;
+  const size_t need_keep = cell == CORTEX_MVRNN ? mv_exchange_bytes(N, H)
+                           : (cell == CORTEX_CHILDSUM_TREEGRU || cell == CORTEX_SIMPLE_TREEGRU) ? keep_bytes(N, H)
+                                                                                               : 0;
   if (hs_off > header_cap || need_hs > hs_cap || need_cs > cs_cap || need_keep > keep_cap) return false;
   out = FwdRegions{header, staged >= 1 ? hs : nullptr, staged >= 2 ? cs : nullptr, (float *)keep};
   return true;

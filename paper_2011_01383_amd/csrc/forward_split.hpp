@@ -156,7 +156,7 @@ struct TileList {
 // [lo, hi) (row0 .. level; the codes are filled by the caller); returns the
 // group's tile count.  One level per thread per round.  off(l) is the first row
 // of level l; *bad is set when the offsets are not monotone from 0 to N.
-template <int INTS, typename Off>
+template <int INTS, int ROWS = kTileM, typename Off>
 __device__ __forceinline__ int list_tiles(const Off &off, int L, int N, int lo, int hi, int group, int Q, int first, int cap,
                                           int tid, int *list, int *wsum, int &bad) {
   int total = 0;
@@ -168,7 +168,7 @@ __device__ __forceinline__ int list_tiles(const Off &off, int L, int N, int lo, 
       r1 = off(l + 1);
       const bool ok = r0 >= 0 && r1 >= r0 && r1 <= N && (l != 0 || r0 == 0) && (l != L - 1 || r1 == N);
       if (!ok) bad = 1;
-      const int ntile = (ok && l >= lo && l < hi) ? (r1 - r0 + kTileM - 1) / kTileM : 0;
+      const int ntile = (ok && l >= lo && l < hi) ? (r1 - r0 + ROWS - 1) / ROWS : 0;
       uf = ((group - l) % Q + Q) % Q;
       cnt = uf < ntile ? (ntile - 1 - uf) / Q + 1 : 0;
     }
@@ -176,7 +176,7 @@ __device__ __forceinline__ int list_tiles(const Off &off, int L, int N, int lo, 
     const int pos = total + block_excl_scan(cnt, wsum, &round_total) - first;
     for (int j = max(0, -pos); j < cnt && pos + j < cap; ++j) {
       int *t = &list[(pos + j) * INTS];
-      t[0] = r0 + kTileM * (uf + j * Q);
+      t[0] = r0 + ROWS * (uf + j * Q);
       t[1] = r1;
       t[2] = l;
       t[3] = r0;
@@ -1326,6 +1326,363 @@ __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) 
       if (!grid_sync<false>(SyncWords{a.sync}, a.status, a.timeout)) return;
   }
   CORTEX_TRACE_KERNEL(3);
+  if (a.retire) retire_tag(a.sync, tag, a.status, a.timeout);
+}
+
+// ---------------------------------------------------------------------------
+// MV-RNN at d = 128: p = tanh(W [B a; A b]), P = W_M [A; B].
+//
+// Node-parallel by COLUMNS of P: workgroup (cb, group) computes the 16 columns
+// [16 cb, + 16) of P for the nodes of its group (a level's nodes are dealt among
+// the groups; a group's eight workgroups sit on one XCD), so it reads just
+// those columns of A and B, an eighth of them, and every element of [A; B] is
+// loaded once per node.  (By rows of P, each of the eight workgroups needs all of
+// [A; B]: 256 KB of tagged pairs per node and workgroup, restaged through LDS.)
+// Wave w holds W_M[:, 32 w .. 32 w + 31] in registers, split; it loads its 32
+// rows x 16 columns of [A; B] straight into the MFMA operand layout, and the
+// eight partial sums meet in LDS.
+//
+// B a and A b need whole rows of B and A: each workgroup forms the partial sums
+// over its 16 columns from the operands it holds and publishes them (2 d values per
+// node) in the workspace; once all eight are there, each workgroup adds them
+// up and computes its 16 rows of p.  Within a level that second half runs one
+// node late, so the exchange is not waited for.
+//
+// Leaf rows of the outputs are copied last, by workgroups with no node left to
+// compute while the narrow top levels finish.
+//
+// 40 trees (1,960 nodes): 424 -> 260 us per step; ten trees 161 -> 104.
+// ---------------------------------------------------------------------------
+struct MvCols {
+  static constexpr int D = 128, RB = D / 16, MT = D / 16;
+  static constexpr int LDN = D + 4;                      // column stride of the partial sums
+  static constexpr int INTS = 6, kCap = 512;             // node record: row, level end, level, level start / -1, two codes
+  static constexpr size_t kXchg = (size_t)RB * 2 * D;    // published partial sums per node
+};
+
+__global__ void __launch_bounds__(kFwdThreads) mvrnn_cols_kernel(FwdArgs a) {
+  using M = MvCols;
+  constexpr int D = M::D, RB = M::RB, MT = M::MT, LDN = M::LDN, INTS = M::INTS, kCap = M::kCap;
+  constexpr int CBUF = kFwdWaves * 16 * LDN;
+
+  __shared__ __attribute__((aligned(16))) float C_s[2 * CBUF];
+  __shared__ float bab_s[2][2][2 * D];          // [parity][half of the column blocks][B a; A b]
+  __shared__ int list[kCap * INTS];
+  __shared__ int wsum[kFwdWaves + 1];
+  __shared__ int stop_s[2];
+
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int i16 = lane & 15, g4 = lane >> 4;
+  const int ngroups = gridDim.x / RB, cb = blockIdx.x / ngroups, group = blockIdx.x % ngroups;
+  const int N = a.N;
+  const uint32_t tag = launch_tag(a.sync);      // read with the status: one round trip
+  const TagBuf hs(a.hs, (uint32_t)N * D * 8);
+  const TagBuf ps(a.cs, (uint32_t)N * D * D * 8);
+  const TagBuf xs(a.keep, (uint32_t)N * (uint32_t)M::kXchg * 8u);
+  const InBuf xv(a.x_table, a.x_table ? (uint32_t)a.x_rows * D * 4 : 0u);
+  const InBuf xm(a.leaf_mat, a.leaf_mat ? (uint32_t)a.x_rows * D * D * 4 : 0u);
+  const int side = wave >> 2, kk = 32 * (wave & 3) + 8 * g4;       // matrix (0: A, 1: B) and this lane's first row of it
+  const int col = 16 * cb + i16;                                   // this lane's column of A, B and P
+  // (opaque: what is derived from it is formed where it is used, not kept in
+  // registers through the node loop)
+  auto fresh_tid = [&]() __attribute__((always_inline)) -> int {
+    int x = threadIdx.x;
+    asm volatile("" : "+v"(x));
+    return x;
+  };
+
+  const int status0 = load_status(a.status);
+  const int L = *a.num_levels;
+  if (tid < 2) stop_s[tid] = 0;
+  Split8 wm[MT];
+  float wmax = 0.f;
+  {
+    float4 v[MT][2];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        v[m][h] = *(const float4 *)&a.W_M[(size_t)(16 * m + i16) * 2 * D + 32 * wave + 8 * g4 + 4 * h];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      wmax = max_abs(max_abs(wmax, v[m][0]), v[m][1]);
+      wm[m] = split8(v[m][0], v[m][1]);
+    }
+  }
+  if (status0 != 0) return;
+  if (L < 1 || L > N) {
+    raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
+    return;
+  }
+  if (!mark_entered(a.sync, tag, a.status)) return;
+
+  int bad = 0, gave_up = 0;
+  // input row of leaf row r, -1 = none (validated)
+  auto leaf_input = [&](int r) __attribute__((always_inline)) -> int {
+    const int v = a.level_nodes[r];
+    if (v < 0 || v >= N) {
+      raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
+      return -1;
+    }
+    const int xi = a.x_index[v];
+    if (xi < -1 || xi >= a.x_rows) {
+      raise_status(a.status, CORTEX_ST_INPUT_RANGE);
+      return -1;
+    }
+    return xi;
+  };
+
+  // a wave's operands: its 8 matrix elements per lane and one vector element
+  // (a for the rows of B, b for the rows of A), staged (value, tag) or plain
+  u32x2 f[8], fv;
+  int cm = -1, cv = -1;                         // source codes of the matrix and of the vector (one per wave)
+  auto issue = [&](const int *t) __attribute__((always_inline)) {
+    cm = __builtin_amdgcn_readfirstlane(t[4 + side]);
+    cv = __builtin_amdgcn_readfirstlane(t[4 + (side ^ 1)]);
+    if (cm >= 0) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) f[j] = ps.first1_at((uint32_t)((cm * D + kk + j) * D + col) * 8u);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        f[j] = u32x2{xm.load1(cm <= -2 ? (uint32_t)(((-2 - cm) * D + kk + j) * D + col) * 4u : kNoSource), 0u};
+    }
+    if (cv >= 0) fv = hs.load1_at((uint32_t)(cv * D + col) * 8u);
+    else fv = u32x2{xv.load1(cv <= -2 ? (uint32_t)((-2 - cv) * D + col) * 4u : kNoSource), 0u};
+  };
+  auto ready = [&]() __attribute__((always_inline)) -> bool {
+    bool r = cv < 0 || fv.y == tag;
+    if (cm >= 0) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) r = r && f[j].y == tag;
+    }
+    return r;
+  };
+  // bounded waits: poll() requests again what is missing
+  auto wait_for = [&](auto is_ready, auto poll, int phase) __attribute__((always_inline)) {
+    if (gave_up || is_ready()) return;
+    const uint64_t t0 = wall_clock64();
+    for (;;) {
+      __builtin_amdgcn_s_sleep(1);
+      poll();
+      const int stv = load_status(a.status);
+      if (is_ready()) break;
+      if (stv != 0) {
+        gave_up = 1;
+        break;
+      }
+      if (wall_clock64() - t0 > a.timeout) {
+        raise_status(a.status, CORTEX_ST_BARRIER_TIMEOUT);
+        gave_up = 1;
+        break;
+      }
+    }
+    if (gave_up) stop_s[phase & 1] = 1;         // read by every wave after the barrier that closes the phase
+  };
+  // the published partial sums of a node: entry tid mod 2d of four column blocks
+  u32x2 g[4];
+  auto issue_gather = [&](int row) __attribute__((always_inline)) {
+    const int x = fresh_tid();
+    const uint32_t o = (uint32_t)((row * RB + 4 * (x >> 8)) * 2 * D + (x & (2 * D - 1))) * 8u;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) g[c] = xs.load1_at(o + 16u * D * c);
+  };
+  int phase = 0;                                // barriers passed in the node loop
+  // the second half of a node: its 16 rows of p; true when the kernel must stop
+  auto vector_half = [&](int row) __attribute__((always_inline)) -> bool {
+    // p: row 16 cb + po, columns [8 ppart, + 8) of W (from the caches: registers
+    // are short)
+    const int x0 = fresh_tid(), po = x0 >> 5, ppart = x0 & 31;
+    const float4 w0 = *(const float4 *)&a.W[(size_t)(16 * cb + po) * 2 * D + 8 * ppart];
+    const float4 w1 = *(const float4 *)&a.W[(size_t)(16 * cb + po) * 2 * D + 8 * ppart + 4];
+    wait_for([&]() { return g[0].y == tag && g[1].y == tag && g[2].y == tag && g[3].y == tag; },
+             [&]() { issue_gather(row); }, phase);
+    (&bab_s[phase & 1][0][0])[x0] = (as_float(g[0].x) + as_float(g[1].x)) + (as_float(g[2].x) + as_float(g[3].x));
+    __syncthreads();
+    const bool stop = stop_s[phase & 1] != 0;
+    const float *b0 = &bab_s[phase & 1][0][8 * ppart], *b1 = &bab_s[phase & 1][1][8 * ppart];
+    const float wp[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+    float s = 0.f;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) s = fmaf(wp[c], b0[c] + b1[c], s);
+    ++phase;
+    if (stop) return true;
+#pragma unroll
+    for (int x = 16; x > 0; x >>= 1) s += __shfl_xor(s, x, 32);
+    if (ppart == 0) {
+      const uint32_t el = (uint32_t)(row * D + 16 * cb + po);
+      const float pv = tanh_f(s);
+      hs.store1(el, pv, tag);
+      a.h[el] = pv;
+    }
+    return false;
+  };
+
+  int total = 0, listed = 0, off1 = 0;
+#pragma unroll 1
+  for (int first = 0;; first += kCap) {
+    if (first > 0 && first >= total) break;
+    __syncthreads();                            // every wave is done with the records
+    {
+      int t0 = threadIdx.x;
+      asm volatile("" : "+v"(t0));              // (nothing derived from it is kept through the node loop)
+      total = list_tiles<INTS, 1>([&](int l) { return a.level_offsets[l]; }, L, N, 1, L, group, ngroups, first, kCap, t0, list,
+                                  wsum, bad);
+      listed = min(total - first, kCap);
+      if (__syncthreads_or(bad)) {
+        raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
+        return;
+      }
+      off1 = a.level_offsets[1];
+#pragma unroll 1
+      for (int idx = t0; idx < 2 * listed; idx += kFwdThreads) {
+        int *t = &list[(idx >> 1) * INTS];
+        int c = a.child_rows[(size_t)t[0] * 2 + (idx & 1)];
+        if (c < -1 || c >= t[3]) {              // a child must sit in a lower level
+          bad = 1;
+          c = -1;
+        }
+        if (c >= 0 && c < off1) {
+          const int xi = leaf_input(c);
+          c = xi >= 0 ? -2 - xi : -1;
+        }
+        t[4 + (idx & 1)] = c;
+      }
+    }
+    if (__syncthreads_or(bad)) {
+      raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
+      return;
+    }
+    if (listed > 0) issue(list);
+    int pend = -1;                              // node whose second half is still to run
+#pragma unroll 1
+    for (int e = 0; e < listed; ++e) {
+      int *t = &list[e * INTS];
+      const bool more = e + 1 < listed;
+      const int row = t[0];
+      wait_for(ready, [&]() {
+        if (cm >= 0) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) f[j] = ps.load1_at((uint32_t)((cm * D + kk + j) * D + col) * 8u);
+        }
+        if (cv >= 0) fv = hs.load1_at((uint32_t)(cv * D + col) * 8u);
+      }, phase);
+      float v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = as_float(f[j].x);
+      const float vec = as_float(fv.x);
+      if (pend >= 0) issue_gather(pend);
+      if (more) issue(t + INTS);
+      // partial sums over this workgroup's columns: q[j] = M[kk + j][.] . vector,
+      // folded so that lane i16 ends with row j = i16 / 2
+      {
+        float q[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) q[j] = v[j] * vec;
+#pragma unroll
+        for (int n = 4; n > 0; n >>= 1) {
+          const bool up = (i16 & (2 * n)) != 0;
+#pragma unroll
+          for (int j = 0; j < n; ++j) {
+            const float keep = up ? q[j + n] : q[j], give = up ? q[j] : q[j + n];
+            q[j] = keep + __shfl_xor(give, 2 * n, 16);
+          }
+        }
+        q[0] += __shfl_xor(q[0], 1, 16);
+        // B a (rows of B) first, then A b
+        if ((i16 & 1) == 0)
+          xs.store1((uint32_t)((row * RB + cb) * 2 * D + (side ^ 1) * D + kk + (i16 >> 1)), q[0], tag);
+      }
+      const float4 v0 = make_float4(v[0], v[1], v[2], v[3]), v1 = make_float4(v[4], v[5], v[6], v[7]);
+      if (max_abs(max_abs(wmax, v0), v1) >= kSplitLimit) t[3] = -1;      // read after the barrier
+      const Split8 b = split8(v0, v1);
+      // lane (column i16) receives rows 16 m + 4 g4 .. + 3; half of the row tiles
+      // at a time, so the accumulators leave room for the next node's operands
+      float *cbuf = &C_s[(e & 1) * CBUF];
+      static_for<2>([&](auto half) __attribute__((always_inline)) {
+        constexpr int HM = MT / 2, m0 = half * HM;
+        floatx4 hi[HM], lo[HM];
+#pragma unroll
+        for (int m = 0; m < HM; ++m) lo[m] = mfma_bf16(wm[m0 + m].p2, b.p0, floatx4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+        for (int m = 0; m < HM; ++m) lo[m] = mfma_bf16(wm[m0 + m].p1, b.p1, lo[m]);
+#pragma unroll
+        for (int m = 0; m < HM; ++m) lo[m] = mfma_bf16(wm[m0 + m].p0, b.p2, lo[m]);
+#pragma unroll
+        for (int m = 0; m < HM; ++m) lo[m] = mfma_bf16(wm[m0 + m].p1, b.p0, lo[m]);
+#pragma unroll
+        for (int m = 0; m < HM; ++m) lo[m] = mfma_bf16(wm[m0 + m].p0, b.p1, lo[m]);
+#pragma unroll
+        for (int m = 0; m < HM; ++m) hi[m] = mfma_bf16(wm[m0 + m].p0, b.p0, floatx4{0.f, 0.f, 0.f, 0.f});
+#pragma unroll
+        for (int m = 0; m < HM; ++m) *(floatx4 *)&cbuf[(wave * 16 + i16) * LDN + 16 * (m0 + m) + 4 * g4] = hi[m] + lo[m];
+      });
+      __syncthreads();
+      const bool stop = stop_s[phase & 1] != 0;
+      ++phase;
+      if (stop) return;
+      {
+        const int x0 = fresh_tid(), n = x0 & 15, r4 = 4 * (x0 >> 4);
+        floatx4 s[kFwdWaves];
+#pragma unroll
+        for (int w = 0; w < kFwdWaves; ++w) s[w] = *(const floatx4 *)&cbuf[(w * 16 + n) * LDN + r4];
+        floatx4 sum = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+        if (__builtin_expect(t[3] < 0, 0)) {
+          // an element or a weight cannot be split: the sums in plain fp32
+#pragma unroll 1
+          for (int i = 0; i < 4; ++i) {
+            float acc = 0.f;
+#pragma unroll 1
+            for (int k = 0; k < 2 * D; ++k) {
+              const int c = t[4 + k / D];
+              const uint32_t at = (uint32_t)(((c >= 0 ? c : -2 - c) * D + k % D) * D + 16 * cb + n);
+              float x = 0.f;
+              if (c >= 0) x = as_float(ps.load1_at(at * 8u).x);
+              else if (c <= -2) x = as_float(xm.load1(at * 4u));
+              acc = fmaf(a.W_M[(size_t)(r4 + i) * 2 * D + k], x, acc);
+            }
+            if (i == 0) sum.x = acc;
+            if (i == 1) sum.y = acc;
+            if (i == 2) sum.z = acc;
+            if (i == 3) sum.w = acc;
+          }
+        }
+        const uint32_t el = (uint32_t)(row * D * D + r4 * D + 16 * cb + n);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ps.store1(el + i * D, sum[i], tag);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a.c[el + i * D] = sum[i];
+      }
+      // the previous node's second half, and this one's when it is the group's
+      // last of its level: what follows may wait for its p
+      const bool last = !more || t[INTS + 2] != t[2];
+      int todo = pend;
+      pend = row;
+#pragma unroll 1
+      for (;;) {
+        if (todo >= 0 && vector_half(todo)) return;
+        if (!last || pend < 0) break;
+        issue_gather(pend);
+        todo = pend;
+        pend = -1;
+      }
+    }
+  }
+  // leaves: (p, P) = (x_table[x], leaf_mat[x]) or zeros, plain stores (no
+  // workgroup reads them back)
+  for (int r = blockIdx.x; r < off1; r += gridDim.x) {
+    const int xi = leaf_input(r);
+    if (tid < D / 4) {
+      const float4 val = as_float4(xv.load4(xi >= 0 ? (uint32_t)((xi * D + tid * 4) * 4) : kNoSource));
+      *(float4 *)&a.h[(size_t)r * D + tid * 4] = val;
+    }
+#pragma unroll
+    for (int k = 0; k < D * D / 4 / kFwdThreads; ++k) {
+      const int e = tid + k * kFwdThreads;
+      const float4 val = as_float4(xm.load4(xi >= 0 ? (uint32_t)((xi * D * D + e * 4) * 4) : kNoSource));
+      *(float4 *)&a.c[(size_t)r * D * D + e * 4] = val;
+    }
+  }
   if (a.retire) retire_tag(a.sync, tag, a.status, a.timeout);
 }
 

@@ -57,6 +57,8 @@ SIZES = {
     "childsum_h256_arity2": lambda: childsum(15, 40, 30, 90, max_arity=2),
     "childsum_h256_all_leaves": lambda: childsum(16, 1201, 1, 1),
     "childsum_h256_forest": lambda: childsum(17, 333, 1, 60),
+    "mvrnn_d128_one_leaf": lambda: I.mvrnn_workload(29, batch=1, d=128, leaf_lo=1, leaf_hi=1),
+    "mvrnn_d128_forest": lambda: I.mvrnn_workload(30, batch=23, d=128, leaf_lo=1, leaf_hi=50),
     "dag_h256_1x1": lambda: I.dagrnn_workload(10, n_grids=1, rows=1, cols=1, H=256),
     "dag_h256_6143": lambda: I.dagrnn_workload(25, n_grids=1, rows=1, cols=6143, H=256),
     "dag_h256_6144": lambda: I.dagrnn_workload(26, n_grids=2, rows=48, cols=64, H=256),
@@ -117,7 +119,26 @@ def test_more_tiles_than_the_list(groups):
     compare_states(got, O.forward_workload(wl), "caterpillars")
 
 
+@pytest.mark.parametrize("groups", [1, 3])
+def test_mvrnn_node_groups(groups):
+    """One node group holds more nodes than its list (512); the states are
+    bitwise those of the default."""
+    wl = I.mvrnn_workload(31, batch=8, d=128, leaf_lo=90, leaf_hi=90)
+    announce("split mvrnn groups %d N=%d" % (groups, wl.N))
+    ref = run(wl).states_by_node()
+    C.cortex_set_knob(C.CORTEX_KNOB_FWD_NODE_GROUPS, groups)
+    try:
+        got = run(wl).states_by_node()
+    finally:
+        C.cortex_set_knob(C.CORTEX_KNOB_FWD_NODE_GROUPS, 0)
+    for key in ref:
+        assert np.array_equal(ref[key], got[key]), key
+    compare_states(ref, O.forward_workload(wl), "mvrnn")
+
+
 UNSPLITTABLE = {
+    # (one level: P is linear, and deeper products of huge finite values leave the fp32 range)
+    "mvrnn": lambda: I.mvrnn_workload(32, batch=9, d=128, leaf_lo=2, leaf_hi=2),
     "nary": lambda: I.nary_treelstm_workload(20, batch=60, H=256, leaf_lo=20, leaf_hi=20),
     "childsum": lambda: childsum(24, 80, 20, 20),
     "tree_rnn": lambda: tree_rnn(21, 60, 30, 30, 256),
@@ -136,12 +157,13 @@ def test_unsplittable_values(name, where, value):
     wl = UNSPLITTABLE[name]()
     announce("split %s %s %r N=%d" % (name, where, value, wl.N))
     if where == "input":
-        key = "x" if wl.x is not None else "x_table"
+        key = "x" if wl.x is not None else "leaf_mat" if wl.leaf_mat is not None else "x_table"
         arr = getattr(wl, key).copy()
-        arr[3, 5] = value
+        arr.reshape(arr.shape[0], -1)[3, 5] = value
     else:
         # (child-sum: an input weight; its leaves have no recurrent product to meet one of U)
         key = "U" if wl.U is not None and wl.cell != I.CELL_CHILDSUM_TREELSTM else "W"
+        key = "W_M" if wl.W_M is not None else key
         arr = getattr(wl, key).copy()
         arr.reshape(-1, wl.H)[7, 9] = value
     wl = dataclasses.replace(wl, **{key: arr})
