@@ -2117,8 +2117,8 @@ __global__ void __launch_bounds__(kFwdThreads) treegru_forward_kernel(FwdArgs a)
 #pragma unroll
         for (int b = 0; b < NBE; ++b) {
           const uint32_t so = ecr >= 0 ? (uint32_t)(ecr * H + ek + 16 * b) * 8u : kNoSource;
-          ev[b].lo = hs.load2_at(so);
-          ev[b].hi = hs.load2_at(so + 16u);
+          ev[b].lo = hs.first2_at(so);
+          ev[b].hi = hs.first2_at(so + 16u);
         }
         const int icr = (tid < kTileM * ZW && zk >= 2) ? child(u, zi, zk - 2) : -1;
         const int ie = icr >= 0 ? icr * H + hbase + zj : -1;
@@ -2249,8 +2249,8 @@ __global__ void __launch_bounds__(kFwdThreads) treegru_forward_kernel(FwdArgs a)
 #pragma unroll
         for (int b = 0; b < NBB; ++b) {
           const uint32_t so = mrow < r1 ? (uint32_t)(mrow * H + wave * KWB + 16 * b + 4 * g4) * 8u : kNoSource;
-          mf[b].lo = ms.load2_at(so);
-          mf[b].hi = ms.load2_at(so + 16u);
+          mf[b].lo = ms.first2_at(so);
+          mf[b].hi = ms.first2_at(so + 16u);
         }
         auto ready_b = [&]() __attribute__((always_inline)) -> bool {
           bool r = true;
@@ -2546,8 +2546,8 @@ __global__ void __launch_bounds__(MvDims<D>::kThreads) mvrnn_forward_kernel(FwdA
         const int st = src_s[side][0], xi = src_s[side][1];
         if (st >= 0) {
           const uint32_t so = (uint32_t)(st * D * D + e4) * 8u;
-          lo[k] = ps.load2_at(so);
-          hi[k] = ps.load2_at(so + 16u);
+          lo[k] = ps.first2_at(so);
+          hi[k] = ps.first2_at(so + 16u);
         } else {
           lo[k] = xm.load4(xi >= 0 ? (uint32_t)((xi * D * D + e4) * 4) : kNoSource);
           hi[k] = u32x4{0u, 0u, 0u, 0u};
