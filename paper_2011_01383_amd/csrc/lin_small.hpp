@@ -202,9 +202,9 @@ __device__ bool height_dataflow(const int (&lc)[PER][4], const int (&ext)[PER][4
   return complete;
 }
 
-// Sweeps to the fixed point over child slots [0, KS).  Returns (uniformly
-// over the workgroup) whether any height changed; *cycle is set when a value
-// reached N.  Every thread of the workgroup calls it.
+// Sweeps to the fixed point over child slots [0, KS).  Returns whether a height
+// of the calling thread changed; *cycle is set (uniformly over the workgroup)
+// when a value reached N.  Every thread of the workgroup calls it.
 template <int PER, int THREADS, int KS, bool BLK = false>
 __device__ bool relax_heights_k(const int (&lc)[PER][4], const int (&ext)[PER][4], int (&myh)[PER], int *hs, int n,
                                 int N, bool *cycle, int *sweeps) {
@@ -224,7 +224,7 @@ __device__ bool relax_heights_k(const int (&lc)[PER][4], const int (&ext)[PER][4
     }
     if (!__syncthreads_or(ch)) break;
   }
-  return __syncthreads_or(any) != 0;
+  return any;
 }
 
 template <int PER, int THREADS, bool BLK = false>

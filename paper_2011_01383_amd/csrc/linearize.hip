@@ -167,12 +167,42 @@ __global__ void __launch_bounds__(kLinThreads, kDual ? 8 : 1) linearize_kernel(L
   // from LDS, gets its first histograms from the height rounds, and the
   // child rows are written per node
   const bool own_tile = a.chunk == kTile && G == T && in_regs;
+  // Which rounds are needed: a chunk is at its fixed point for the outside
+  // heights it read, so the whole is at its fixed point once no height that
+  // another chunk reads has changed since those were published.  The nodes that
+  // other chunks read are marked in round 0, in node_row (written with rows only
+  // after the height rounds; a stale mark would cost a round, nothing else), and
+  // each owner then reports changes of marked nodes alone.  Trees shorter than a
+  // chunk straddle one boundary: their upper part changes in round 1, but nobody
+  // reads it, so the round that would only confirm it goes (10,000 nodes of 200
+  // trees: 3 rounds -> 2, linearization 34 -> 27 us).
+  constexpr int kMarked = -7;
+  const bool use_marks = a.chunk <= kLinPer * kLinThreads;
+  bool marked[kLinPer];
+#pragma unroll
+  for (int j = 0; j < kLinPer; ++j) marked[j] = true;
+  if (use_marks && ok) {
+#pragma unroll
+    for (int j = 0; j < kLinPer; ++j)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        if (cid[j][s] >= 0 && lc[j][s] < 0)
+          __hip_atomic_store(&a.node_row[cid[j][s]], kMarked, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   int round = 0;
   int L = 0;
   while (ok) {
     int block_changed = (round == 0) && has_ext;
     int local_max = 0;
     if (in_regs) {
+      int before[kLinPer];
+#pragma unroll
+      for (int j = 0; j < kLinPer; ++j) {
+        before[j] = myh[j];
+        const int i = owned_node<kLinPer, kLinThreads, true>(j);
+        if (use_marks && round == 1)
+          marked[j] = i < n && __hip_atomic_load(&a.node_row[lo + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kMarked;
+      }
       // children outside the chunk keep one height per round: 0 in round 0
       // (a lower bound), then what the previous round published
 #pragma unroll
@@ -188,9 +218,15 @@ __global__ void __launch_bounds__(kLinThreads, kDual ? 8 : 1) linearize_kernel(L
       // (round 0 reports has_ext alone: a chunk without outside children
       // is exact whatever its sweeps changed.  When the dataflow pass
       // computed every node, round 0 needs no sweep at all.)
-      if (!(round == 0 && complete0) &&
-          relax_heights<kLinPer, kLinThreads, true>(lc, ext, myh, hs, n, K, N, &cyc, &sweeps0) && round > 0)
-        block_changed = 1;
+      if (!(round == 0 && complete0)) {
+        relax_heights<kLinPer, kLinThreads, true>(lc, ext, myh, hs, n, K, N, &cyc, &sweeps0);
+        if (round > 0) {
+          int seen = 0;
+#pragma unroll
+          for (int j = 0; j < kLinPer; ++j) seen |= marked[j] && myh[j] != before[j];
+          block_changed = __syncthreads_or(seen);
+        }
+      }
       if (cyc && tid == 0) raise_status(a.status, CORTEX_ST_CYCLE);
     } else for (;;) {
       int changed = 0, cyc = 0;

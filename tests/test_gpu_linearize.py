@@ -323,3 +323,40 @@ def test_multi_workgroup_node_limit():
     assert C.cortex_linearize(children, N, 2, lin, status, ws) == C.CORTEX_E_TOO_LARGE
     torch.cuda.synchronize()
     assert int(status.item()) == 0
+
+
+@pytest.mark.parametrize("shape", ["straddling", "spanning", "shuffled", "reversed"])
+def test_heights_across_chunks(shape):
+    """Batches whose chunks (1,024 nodes) read each other's heights: trees that
+    straddle one boundary, one tree spanning every chunk (its heights take a round
+    per chunk on the way up), ids shuffled (every chunk reads every other) and ids
+    reversed (children above their parents); run twice on the same arrays, which
+    then hold the first run's rows."""
+    rng = np.random.default_rng(77)
+    if shape == "spanning":
+        trees = [I.caterpillar(3000)]
+    else:
+        trees = [I.random_split_tree(rng, int(n)) for n in rng.integers(1, 60, size=180)]
+    children, is_leaf = I.forest_to_children(trees, 2)
+    N = is_leaf.size
+    if shape == "shuffled":
+        children = I.relabel(children, 2, rng.permutation(N).astype(np.int32))
+    elif shape == "reversed":
+        children = I.relabel(children, 2, np.arange(N - 1, -1, -1, dtype=np.int32))
+    assert N > 4096
+    announce("linearize across chunks %s N=%d" % (shape, N))
+    lin = C.Linearization.alloc(N, 2)
+    dev = torch.from_numpy(children).cuda()
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = C.workspace(C.cortex_linearize_workspace_bytes(N, 2))
+    ref = O.linearize(children, 2)
+    for _ in range(2):
+        C.check(C.cortex_linearize(dev, N, 2, lin, status, ws))
+        torch.cuda.synchronize()
+        assert int(status.item()) == 0
+        L = int(lin.num_levels.item())
+        got = {"num_levels": L, "height": lin.height[:N].cpu().numpy(),
+               "level_offsets": lin.level_offsets[:L + 1].cpu().numpy(),
+               "level_nodes": lin.level_nodes[:N].cpu().numpy(), "node_row": lin.node_row[:N].cpu().numpy(),
+               "child_rows": lin.child_rows[:2 * N].cpu().numpy()}
+        compare_lin(got, ref, 2)

@@ -7,7 +7,7 @@ import dataclasses
 import numpy as np
 import pytest
 
-from gpu_helpers import announce, compare_states, need_gpu
+from tests.gpu_helpers import announce, compare_states, need_gpu
 
 torch = pytest.importorskip("torch")
 
