@@ -86,7 +86,8 @@ def bound_of(flops, byts):
     return "mfma" if t_f >= t_b else "hbm"
 
 
-FORWARD_SOURCES = ("paper_2011_01383_amd/csrc/forward.hip", "paper_2011_01383_amd/csrc/cortex_device.hpp",
+FORWARD_SOURCES = ("paper_2011_01383_amd/csrc/forward.hip", "paper_2011_01383_amd/csrc/forward_split.hpp",
+                   "paper_2011_01383_amd/csrc/cortex_device.hpp",
                    "paper_2011_01383_amd/csrc/cortex_host.hpp", "paper_2011_01383_amd/csrc/lin_small.hpp")
 
 

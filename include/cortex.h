@@ -217,8 +217,9 @@ int cortex_tree_forward(int32_t cell, int32_t H, const cortex_lin_t *lin, const 
  * cortex_linearize (written to *lin) followed by cortex_tree_forward, with the
  * arguments and results of those two calls (N and K are taken from lin).
  * Where the cell has a fused instance -- TreeRNN (H = 64 up to 320 nodes,
- * 256, 512), N-ary TreeLSTM (64, 256), child-sum TreeLSTM and the TreeGRU
- * cells (64, 256, 512), MV-RNN (d = 64); N <= 2048, the schedule knobs at their defaults
+ * 256, 512), N-ary TreeLSTM (64; 256 up to 1,536 nodes), child-sum TreeLSTM
+ * (64, 512; 256 below 1,200 nodes), the TreeGRU cells (64, 256, 512), MV-RNN
+ * (d = 64); N <= 2048, the schedule knobs at their defaults
  * (FWD_NODE_GROUPS aside) and the batch's linearization and structure
  * fitting one compute unit's LDS beside the kernel's own -- this is ONE
  * kernel launch: every workgroup linearizes the batch in LDS for itself (the
@@ -254,7 +255,8 @@ int cortex_tree_infer(int32_t cell, int32_t H, const int32_t *d_children, const 
  *     launches) at most 2 MiB; N * H at most 2,097,152 for the h staging;
  *     the second state's staging (c and the TreeGRU reset sums: N * H; P of
  *     MV-RNN: N * H * H) at most 4,194,304 elements; the TreeGRU phase values
- *     (N * H * 3 floats) at most 8 MiB.  A batch beyond them returns
+ *     (N * H * 3 floats) or the MV-RNN exchange at d = 128 (16 KiB per node)
+ *     at most 8 MiB.  A batch beyond them returns
  *     CORTEX_E_WORKSPACE and enqueues nothing.  Other host errors are those of
  *     cortex_tree_infer, also with nothing enqueued.
  *   - Each call enqueues, before the path's own launches, one small kernel
@@ -292,8 +294,7 @@ int cortex_dag_forward(int32_t H, const cortex_lin_t *lin, const float *d_x, con
  * The whole hot path of a DAG-RNN batch in one call: cortex_linearize, then
  * cortex_dag_forward, with the arguments and results of those two calls.  One
  * kernel launch where the batch fits the fused instance of the kernel with
- * 16-unit slices (H = 64 or 512, or 256 below the 64-unit kernel's range of
- * 6144 nodes; N <= 2048, default schedule knobs, the linearization fitting
+ * 16-unit slices (N <= 2048, default schedule knobs, the linearization fitting
  * one compute unit's LDS beside the weight slice): every workgroup linearizes
  * the batch in LDS and workgroup 0 writes *lin out.  Otherwise the two calls.
  *   d_ws   cortex_dag_infer_workspace_bytes(N, K, H) bytes, zeroed before first use
