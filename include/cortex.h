@@ -330,7 +330,8 @@ int cortex_dag_infer(int32_t H, const int32_t *d_children, const cortex_lin_t *l
  *                                   TreeLSTM at H = 256; 16 or 64 for the
  *                                   DAG-RNN at H = 256, whose default is 64
  *                                   for batches of at least 36,864 nodes, 32
- *                                   from 6,144 and 16 below)
+ *                                   from 6,144 (64 there too with more node
+ *                                   groups than fit beside 32) and 16 below)
  *   CORTEX_KNOB_LEVEL_SYNC          how the forward orders its levels, for
  *                                   ablation studies (the results are the same):
  *                                   0 = per-datum waits in one launch (default);

@@ -2789,10 +2789,12 @@ static bool pick(int cell, int H, int32_t N, int32_t K, bool cached, Instance &o
   // latency-bound); the knob forces 16 or 64.  us per step (16 / 32 / 64 units),
   // grids of 32x32: 6 grids 249 / 257 / 280, 12: 284 / 265 / 288, 20: 320 / 287 /
   // 303, 32: 402 / 327 / 333, 48: 537 / 377 / 360, 64: 672 / 434 / 385, 250:
-  // 2,490 / - / 938; 10x10: 40 grids 109 / 109 / 120, 64: 123 / 115 / 126
+  // 2,490 / - / 938; 10x10: 40 grids 109 / 109 / 120, 64: 123 / 115 / 126.
+  // More node groups than fit beside eight slices also take the 64-unit kernel,
+  // which has four
   if (cell == CELL_DAG && H == kDagH && (units == 64 || (units != 16 && N >= kDagWideMinRows))) {
     const bool hoisted = knob(CORTEX_KNOB_ABLATE) & 4;       // the input products in dag_input_gemm_kernel
-    if (hoisted || units == 64 || N >= kDag64MinRows) {
+    if (hoisted || units == 64 || N >= kDag64MinRows || groups > num_cus() / (kDagH / 32)) {
       pick_split<CELL_DAG, kDagH, kDagJ>(out, N);
       out.fn = hoisted ? slice_split_kernel<CELL_DAG, kDagH, kDagJ, false, false, true>
                        : slice_split_kernel<CELL_DAG, kDagH, kDagJ, false>;

@@ -119,6 +119,21 @@ def test_more_tiles_than_the_list(groups):
     compare_states(got, O.forward_workload(wl), "caterpillars")
 
 
+@pytest.mark.parametrize("groups,units", [(32, 32), (33, 64), (64, 64)])
+def test_dag_node_groups(groups, units):
+    """Every group count that some slice width has room for (256 compute units)
+    runs, on the narrowest such slices."""
+    wl = I.dagrnn_workload(33, n_grids=2, rows=48, cols=64, H=256)
+    announce("split dag groups %d N=%d" % (groups, wl.N))
+    C.cortex_set_knob(C.CORTEX_KNOB_FWD_NODE_GROUPS, groups)
+    try:
+        got = run(wl).states_by_node()
+        assert C.cortex_last_grid(1) == groups * (256 // units)
+    finally:
+        C.cortex_set_knob(C.CORTEX_KNOB_FWD_NODE_GROUPS, 0)
+    compare_states(got, O.forward_workload(wl), "dag")
+
+
 @pytest.mark.parametrize("groups", [1, 3])
 def test_mvrnn_node_groups(groups):
     """One node group holds more nodes than its list (512); the states are
