@@ -16,9 +16,11 @@
 // addends shows: 0.91e-7 / 2.3e-7 / 4.9e-7.)
 //
 // Values that round to infinity in bf16 (infinities, |x| >= 3.396e38) cannot be
-// split; where a tile's operands or the weights hold one, the tile's sums are
-// formed again from the fp32 values (rare, slow and plain).  NaN needs no such
-// path: it stays NaN in every plane.
+// split, and where products of finite values leave the fp32 range, plane products
+// of both signs would (hi + lo is then infinity minus infinity).  Where a tile's
+// operands or the weights allow either (split_limit), the tile's sums are formed
+// again from the fp32 values (rare, slow and plain).  NaN needs no such path: it
+// stays NaN in every plane.
 #pragma once
 
 namespace cortex {
@@ -74,6 +76,24 @@ __device__ __forceinline__ void static_for(F f) {
 constexpr float kSplitLimit = 3.3961775e38f;
 __device__ __forceinline__ float max_abs(float m, const float4 v) {
   return fmaxf(fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
+}
+// The operand magnitude from which a wave whose weights reach wmax (this lane's
+// share of them) must not use the planes: below it no sum of `terms` products can
+// pass half of FLT_MAX, so no plane product or sum of them overflows.  Every
+// magnitude, zero included, when a weight itself cannot be split.  Called by
+// whole waves; the same value in every lane.
+__device__ __forceinline__ float split_limit(float wmax, int terms) {
+  // (rotations within 16 lanes, then one lane of each: no index registers, as
+  // shuffles would take)
+  static_for<4>([&](auto i) __attribute__((always_inline)) {
+    const int x = (int)as_uint(wmax);
+    wmax = fmaxf(wmax, as_float((unsigned int)__builtin_amdgcn_update_dpp(x, x, 0x120 + (8 >> i), 0xf, 0xf, false)));
+  });
+  const int x = (int)as_uint(wmax);
+  wmax = fmaxf(fmaxf(as_float((unsigned int)__builtin_amdgcn_readlane(x, 0)), as_float((unsigned int)__builtin_amdgcn_readlane(x, 16))),
+               fmaxf(as_float((unsigned int)__builtin_amdgcn_readlane(x, 32)), as_float((unsigned int)__builtin_amdgcn_readlane(x, 48))));
+  const float limit = wmax >= kSplitLimit ? -1.f : fminf(kSplitLimit, 1.6e38f / ((float)terms * wmax));
+  return as_float(__builtin_amdgcn_readfirstlane(as_uint(limit)));     // (a scalar register)
 }
 
 __device__ __forceinline__ floatx4 mfma_bf16(bf16x8 a, bf16x8 b, floatx4 c) {
@@ -458,7 +478,14 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
     }
     off1 = a.level_offsets[1];
   }
-  if constexpr (!kWeightsFromMemory) split_weights(wv);
+  if constexpr (!kWeightsFromMemory) {
+    split_weights(wv);
+  } else {
+#pragma unroll 1
+    for (int k = 0; k < (XS + RS) * NT * 2; ++k) wmax = max_abs(wmax, wfrag(k / (2 * NT), k / 2 % NT, k & 1, i16));
+  }
+  const float limit = split_limit(wmax, D::KX + D::KR);
+  constexpr float kLeast = kDag ? 1.f : 0.f;    // (DAG-RNN: every staged value is a tanh)
 
   int gave_up = 0, lvl = lvl_lo;
   u32x4 flo[2 * RS], fhi[2 * RS];     // staged child pairs: block b = columns rcol + 16 b .. +3
@@ -599,7 +626,7 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
     }
     // a tile's accumulators, and the largest operand met
     floatx4 hi[NT], lo[NT];
-    float mx = wmax;
+    float mx = kLeast;
     // 32 columns of step s: v0, v1 are this lane's four columns of its two blocks
     auto contract = [&](auto s, const float4 v0, const float4 v1, auto between) __attribute__((always_inline)) {
       if constexpr (kWeightsFromMemory) {
@@ -607,7 +634,6 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
           const float4 w0 = wfrag(s, nt, 0, i16), w1 = wfrag(s, nt, 1, i16);
-          mx = max_abs(max_abs(mx, w0), w1);
           wm[nt] = split8(w0, w1);
         }
         mfma_split<NT>(split8(v0, v1), wm, hi, lo, between);
@@ -638,7 +664,7 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
       // the part that waits for nothing
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) hi[nt] = lo[nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-      mx = wmax;
+      mx = kLeast;
       if constexpr (XS > 0) {
 #pragma unroll
         for (int b = 0; b < 2 * XS; ++b) mx = max_abs(mx, as_float4(xv[b]));
@@ -694,7 +720,6 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
         // registers whose values the step took
         static_for<RS>([&](auto s) __attribute__((always_inline)) {
           const float4 v0 = block_value(std::integral_constant<int, 2 * s>{}), v1 = block_value(std::integral_constant<int, 2 * s + 1>{});
-          // (DAG-RNN: every staged value is a tanh)
           if constexpr (kLeafInputs) mx = max_abs(max_abs(mx, v0), v1);
           contract(std::integral_constant<int, XS + s>{}, v0, v1, [&](auto i) __attribute__((always_inline)) {
             // this step's loads, spread over its six products
@@ -705,7 +730,7 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
           });
         });
         cd = cdn;
-        if (mx >= kSplitLimit) list[e * INTS + 3] = -1;     // read after the tile's barrier
+        if (mx >= limit) list[e * INTS + 3] = -1;           // read after the tile's barrier
       }
       CORTEX_TRACE_WAVE(l);
       float *cb = &C_s[kOneBuffer ? 0 : (e & 1) * CBUF];
@@ -894,6 +919,8 @@ __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) 
       wu[s][nt] = split8(wv[1][s][nt][0], wv[1][s][nt][1]);
     }
 
+  const float limit = split_limit(wmax, 5 * D::KW);     // (u: x and the four slots meet in one sum)
+
   auto wx = [&](int s, Split8 (&w)[NT]) __attribute__((always_inline)) {
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
@@ -988,7 +1015,7 @@ __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) 
 #pragma unroll 1
       for (int n = 0; n < cnt; ++n) {
         const int rowbase = LEAF * (group + (first + n) * Q);
-        float mx = wmax;
+        float mx = 0.f;
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
           floatx4 hi[NT], lo[NT];
@@ -1009,7 +1036,7 @@ __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) 
                 C_s[(wave * LEAF + t * kTileM + 4 * g4 + v) * LDL + 16 * nt + i16] = hi[nt][v] + lo[nt][v];
         }
         issue_leaf(n + 1);
-        if (mx >= kSplitLimit) big_s[n & 1] = 1;
+        if (mx >= limit) big_s[n & 1] = 1;
         __syncthreads();
         const bool big = big_s[n & 1] != 0;
         if (tid < LEAF * J) {
@@ -1151,7 +1178,7 @@ __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) 
           if (!grid_sync<false>(SyncWords{a.sync}, a.status, a.timeout)) return;
       }
       CORTEX_TRACE_POINT(l, 0);
-      float mx = wmax;
+      float mx = 0.f;
       // the input part waits for nothing
       floatx4 hi[NT], lo[NT];
 #pragma unroll
@@ -1246,7 +1273,7 @@ __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) 
                          reinterpret_cast<floatx4(&)[HT]>(lo), [](auto) {});
         }
       });
-      if (mx >= kSplitLimit) list[e * INTS + 3] = -1;     // read after the tile's barrier
+      if (mx >= limit) list[e * INTS + 3] = -1;           // read after the tile's barrier
       CORTEX_TRACE_WAVE(l);
       float *cb = &C_s[(e & 1) * CBUF];
 #pragma unroll
@@ -1370,6 +1397,7 @@ __global__ void __launch_bounds__(kFwdThreads) mvrnn_cols_kernel(FwdArgs a) {
   __shared__ int list[kCap * INTS];
   __shared__ int wsum[kFwdWaves + 1];
   __shared__ int stop_s[2];
+  __shared__ float limit_s[kFwdWaves];
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int i16 = lane & 15, g4 = lane >> 4;
@@ -1408,6 +1436,10 @@ __global__ void __launch_bounds__(kFwdThreads) mvrnn_cols_kernel(FwdArgs a) {
       wmax = max_abs(max_abs(wmax, v[m][0]), v[m][1]);
       wm[m] = split8(v[m][0], v[m][1]);
     }
+  }
+  {
+    const float limit = split_limit(wmax, 32);
+    if (lane == 0) limit_s[wave] = limit;       // (in LDS: registers are short; a wave reads its own)
   }
   if (status0 != 0) return;
   if (L < 1 || L > N) {
@@ -1594,7 +1626,7 @@ __global__ void __launch_bounds__(kFwdThreads) mvrnn_cols_kernel(FwdArgs a) {
           xs.store1((uint32_t)((row * RB + cb) * 2 * D + (side ^ 1) * D + kk + (i16 >> 1)), q[0], tag);
       }
       const float4 v0 = make_float4(v[0], v[1], v[2], v[3]), v1 = make_float4(v[4], v[5], v[6], v[7]);
-      if (max_abs(max_abs(wmax, v0), v1) >= kSplitLimit) t[3] = -1;      // read after the barrier
+      if (max_abs(max_abs(0.f, v0), v1) >= limit_s[wave]) t[3] = -1;     // read after the barrier
       const Split8 b = split8(v0, v1);
       // lane (column i16) receives rows 16 m + 4 g4 .. + 3; half of the row tiles
       // at a time, so the accumulators leave room for the next node's operands

@@ -191,3 +191,53 @@ def test_unsplittable_values(name, where, value):
         fine = np.isfinite(r32)
         assert np.array_equal(got[key][~fine & ~np.isnan(r32)], r32[~fine & ~np.isnan(r32)]), key
         assert float(np.abs(got[key][fine] - r32[fine]).max()) <= 1e-4 * max(1.0, float(np.abs(r32[fine]).max())), key
+
+
+BEYOND = dict(
+    UNSPLITTABLE,
+    # (one level: further up the huge weight would magnify the rounding of the states below)
+    nary=lambda: I.nary_treelstm_workload(34, batch=520, H=256, leaf_lo=2, leaf_hi=2),
+    tree_rnn=lambda: tree_rnn(35, 900, 2, 2, 256),
+)
+
+
+@pytest.mark.parametrize("x,w", [(3e38, 2001.3), (-3e38, 2001.3), (2e30, 3e12), (1.0009e30, -3.003e12)])
+@pytest.mark.parametrize("name", sorted(BEYOND))
+def test_products_beyond_the_fp32_range(name, x, w):
+    """Finite inputs and weights, each of which can be split, whose product
+    leaves the fp32 range: the sum is an infinity of that sign, as in fp32
+    arithmetic (a gate saturates), and never NaN from two plane products that
+    overflow with opposite signs."""
+    wl = BEYOND[name]()
+    announce("split %s x %r w %r N=%d" % (name, x, w, wl.N))
+    H, new = wl.H, {}
+    if wl.leaf_mat is not None:
+        # (vectors that keep B a and A b finite)
+        new = {"leaf_mat": wl.leaf_mat.copy(), "x_table": wl.x_table.copy(), "W_M": wl.W_M.copy()}
+        new["leaf_mat"][:, 9, 5] = x
+        new["x_table"][:, 5] = 0.5
+        new["W_M"].reshape(H, 2, H)[7, :, 9] = w
+    else:
+        key = "x" if wl.x is not None else "x_table"
+        new[key] = getattr(wl, key).copy()
+        new[key][:, 9] = x
+        if wl.cell == I.CELL_TREE_RNN:
+            new["W"] = wl.W.copy()
+            new["W"].reshape(H, 2, H)[7, :, 9] = w
+        else:
+            wkey = "U" if wl.cell == I.CELL_NARY_TREELSTM else "W"       # the weights that meet an input row
+            new[wkey] = getattr(wl, wkey).copy()
+            new[wkey].reshape(-1, H, H)[:, 7, 9] = w
+    wl = dataclasses.replace(wl, **new)
+    got = run(wl).states_by_node()
+    with np.errstate(all="ignore"):
+        ref = O.forward_workload(wl)
+        for key in ref:
+            r32 = ref[key].astype(np.float32).astype(np.float64)
+            assert not np.isnan(got[key]).any(), key
+            inf, small = np.isinf(r32), np.abs(r32) <= 16
+            assert np.array_equal(got[key][inf], r32[inf]), key
+            assert float(np.abs(got[key][small] - r32[small]).max()) <= 1e-4, key
+            # input rows (copied) and sums of a few huge products
+            rest = ~inf & ~small
+            assert np.allclose(got[key][rest], r32[rest], rtol=1e-5, atol=0), key
