@@ -255,8 +255,7 @@ int cortex_tree_infer(int32_t cell, int32_t H, const int32_t *d_children, const 
  *     launches) at most 2 MiB; N * H at most 2,097,152 for the h staging;
  *     the second state's staging (c and the TreeGRU reset sums: N * H; P of
  *     MV-RNN: N * H * H) at most 4,194,304 elements; the TreeGRU phase values
- *     (N * H * 3 floats) or the MV-RNN exchange at d = 128 (16 KiB per node)
- *     at most 8 MiB.  A batch beyond them returns
+ *     (N * H * 3 floats) at most 8 MiB.  A batch beyond them returns
  *     CORTEX_E_WORKSPACE and enqueues nothing.  Other host errors are those of
  *     cortex_tree_infer, also with nothing enqueued.
  *   - Each call enqueues, before the path's own launches, one small kernel

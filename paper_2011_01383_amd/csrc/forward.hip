@@ -3214,7 +3214,10 @@ int tree_infer_impl(int32_t cell, int32_t H, const int32_t *d_children, const co
 // Regions of the forward for a workspace placed by the library (the
 // allocation-free entry point): the header and each staging region at their
 // own fixed offsets, whatever the batch, so a region only ever holds its own
-// kind of data.
+// kind of data: tagged pairs in hs and cs, plain floats in keep.  The pairs that
+// MV-RNN exchanges at d = 128 therefore go to the end of the h staging, which its
+// few rows leave free, and not to keep, where a left-over float could read as the
+// launch's tag.
 bool fixed_regions(int32_t cell, int32_t N, int32_t H, void *header, size_t header_cap, void *hs, size_t hs_cap,
                    void *cs, size_t cs_cap, void *keep, size_t keep_cap, FwdRegions &out) {
   size_t hs_off, cs_off, keep_off;
@@ -3222,11 +3225,11 @@ bool fixed_regions(int32_t cell, int32_t N, int32_t H, void *header, size_t head
   const int staged = staged_tensors(cell);
   const size_t need_hs = staged >= 1 ? cs_off - hs_off : 0;
   const size_t need_cs = staged >= 2 ? keep_off - cs_off : 0;
-  const size_t need_keep = cell == CORTEX_MVRNN ? mv_exchange_bytes(N, H)
-                           : (cell == CORTEX_CHILDSUM_TREEGRU || cell == CORTEX_SIMPLE_TREEGRU) ? keep_bytes(N, H)
-                                                                                               : 0;
-  if (hs_off > header_cap || need_hs > hs_cap || need_cs > cs_cap || need_keep > keep_cap) return false;
-  out = FwdRegions{header, staged >= 1 ? hs : nullptr, staged >= 2 ? cs : nullptr, (float *)keep};
+  const size_t need_keep = cell == CORTEX_CHILDSUM_TREEGRU || cell == CORTEX_SIMPLE_TREEGRU ? keep_bytes(N, H) : 0;
+  const size_t pairs = cell == CORTEX_MVRNN ? mv_exchange_bytes(N, H) : 0;
+  if (hs_off > header_cap || need_hs + pairs > hs_cap || need_cs > cs_cap || need_keep > keep_cap) return false;
+  out = FwdRegions{header, staged >= 1 ? hs : nullptr, staged >= 2 ? cs : nullptr,
+                   pairs ? (float *)((char *)hs + (hs_cap - pairs)) : (float *)keep};
   return true;
 }
 

@@ -14,10 +14,10 @@
 //   forward header    barrier words, the staging epoch, entered words (and the
 //                     trace area in trace builds)
 //   linearizer        the workspace of cortex_linearize (two-launch batches)
-//   h staging         tagged (value, tag) pairs of h
+//   h staging         tagged (value, tag) pairs of h; at its end, the pairs
+//                     MV-RNN exchanges at d = 128
 //   second staging    tagged pairs of c, P or the TreeGRU reset sums
-//   phase values      the TreeGRU values kept across a barrier (LEVEL_SYNC 3),
-//                     or the pairs MV-RNN exchanges at d = 128
+//   phase values      the TreeGRU values kept across a barrier (LEVEL_SYNC 3)
 // The staging regions hold nothing but pairs written under the forward
 // header's epoch, so every tag in them is at most the epoch and a launch's tag
 // (the epoch plus one) is never found there before the launch writes it.
@@ -40,7 +40,7 @@ constexpr size_t kPrepBytes = 256;
 constexpr size_t kLinCap = 2u << 20;       // linearizer workspace
 constexpr size_t kHsCap = 16u << 20;       // h staging: N * H <= 2,097,152
 constexpr size_t kCsCap = 32u << 20;       // c / P / reset-sum staging: 4,194,304 pairs
-constexpr size_t kKeepCap = 8u << 20;      // TreeGRU phase values: N * H * 3 floats; MV-RNN pairs
+constexpr size_t kKeepCap = 8u << 20;      // TreeGRU phase values: N * H * 3 floats
 constexpr unsigned long long kClearedMarker = 0x5343524154434832ull;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];

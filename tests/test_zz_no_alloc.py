@@ -4,6 +4,8 @@ library's own device array.  Its results must be bitwise those of
 cortex_tree_infer and within the oracle bound, on consecutive calls whose
 batches shrink (the array keeps the previous call's contents), after a call
 that failed, and it must reject batches beyond its limits on the host."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -62,6 +64,9 @@ PAIRS = {
                 lambda: I.childsum_treegru_workload(108, batch=2, H=256)),
     "mvrnn": (lambda: I.mvrnn_workload(109, batch=6, d=64),
               lambda: I.mvrnn_workload(110, batch=2, d=64)),
+    # the most nodes the staging of P takes at d = 128 (256), then a small batch
+    "mvrnn_d128": (lambda: I.mvrnn_workload(117, batch=2, d=128, leaf_lo=64, leaf_hi=64),
+                   lambda: I.mvrnn_workload(118, batch=2, d=128)),
     "nary_two_launch": (lambda: I.nary_treelstm_workload(111, batch=90, H=256),
                         lambda: I.nary_treelstm_workload(112, batch=40, H=256)),
 }
@@ -99,6 +104,38 @@ def test_call_after_a_failed_call():
     compare_states(st_a, O.forward_workload(good), "after a failed call")
 
 
+def test_left_over_treegru_values_are_no_exchanged_pairs():
+    """TreeGRU with a barrier between its exchanges leaves plain floats in the
+    array; here their bits are every small integer, so also the tag of the next
+    launch.  MV-RNN at d = 128, whose workgroups exchange tagged pairs, must not
+    take them for published values.  One column of matrices holds a value that
+    cannot be split, so the workgroups of that column run late and the others
+    do look before the values are there (its products meet zero weights in p)."""
+    gru = I.childsum_treegru_workload(119, batch=20, H=512, node_lo=50, node_hi=50)
+    W, b = gru.W.copy(), gru.b.copy()
+    W.reshape(3, 512, 512)[2] = 0.0                            # kept: W_h x + b_h = b_h
+    b.reshape(3, 512)[2] = (np.arange(512, dtype=np.uint32) // 2 + 1).view(np.float32)
+    dw = DeviceWorkload(dataclasses.replace(gru, W=W, b=b))
+    wl = I.mvrnn_workload(120, batch=85, d=128, leaf_lo=2, leaf_hi=2)
+    leaf_mat, x_table, Wv = wl.leaf_mat.copy(), 0.1 * wl.x_table, wl.W.copy()
+    leaf_mat[:, 3, 5] = 3.4e38
+    Wv.reshape(128, 2, 128)[:, :, 3] = 0.0
+    wl = dataclasses.replace(wl, leaf_mat=leaf_mat, x_table=x_table, W=Wv)
+    announce("noalloc MV-RNN d=128 N=%d after TreeGRU N=%d with kept values" % (wl.N, dw.N))
+    mv, ref = DeviceWorkload(wl), O.forward_workload(wl)["h"]
+    for _ in range(4):
+        C.cortex_set_knob(C.CORTEX_KNOB_LEVEL_SYNC, 3)
+        try:
+            C.check(noalloc(dw), "cortex_tree_infer_noalloc")
+        finally:
+            C.cortex_set_knob(C.CORTEX_KNOB_LEVEL_SYNC, 0)
+        assert dw.status_code() == 0
+        poison(mv)
+        C.check(noalloc(mv), "cortex_tree_infer_noalloc")
+        assert mv.status_code() == 0
+        compare_states({"h": mv.states_by_node()["h"]}, {"h": ref}, "after kept values")
+
+
 def test_rejects_batches_beyond_its_limits():
     # N * H beyond the h staging region (2,097,152 elements)
     big = I.nary_treelstm_workload(115, batch=1, H=256, leaf_lo=4200, leaf_hi=4200)
@@ -109,6 +146,11 @@ def test_rejects_batches_beyond_its_limits():
     assert noalloc(dw) == C.CORTEX_E_WORKSPACE
     assert dw.status_code() == 0
     assert bool((dw.h == 7.0).all())
+    # N * H * H beyond the staging of P (4,194,304 elements)
+    dw = DeviceWorkload(I.mvrnn_workload(121, batch=2, d=128, leaf_lo=65, leaf_hi=65))
+    assert dw.N == 258
+    assert noalloc(dw) == C.CORTEX_E_WORKSPACE
+    assert dw.status_code() == 0
     # an unsupported hidden size is rejected as by cortex_tree_infer
     small = I.nary_treelstm_workload(116, batch=2, H=64)
     dw = DeviceWorkload(small)
