@@ -18,9 +18,10 @@
 // Values that round to infinity in bf16 (infinities, |x| >= 3.396e38) cannot be
 // split, and where products of finite values leave the fp32 range, plane products
 // of both signs would (hi + lo is then infinity minus infinity).  Where a tile's
-// operands or the weights allow either (split_limit), the tile's sums are formed
-// again from the fp32 values (rare, slow and plain).  NaN needs no such path: it
-// stays NaN in every plane.
+// operands or the weights allow either (split_limit), every wave forms its partial
+// sums of the tile again on the fp32 matrix unit, operands and weights read from
+// memory (one infinite weight, every tile of one slice: 64 grids 402 -> 1,757 us,
+// 200 N-ary trees 188 -> 499, 200 child-sum trees 278 -> 576).  NaN needs no such path: it stays NaN in every plane.
 #pragma once
 
 namespace cortex {
@@ -94,6 +95,14 @@ __device__ __forceinline__ float split_limit(float wmax, int terms) {
                fmaxf(as_float((unsigned int)__builtin_amdgcn_readlane(x, 32)), as_float((unsigned int)__builtin_amdgcn_readlane(x, 48))));
   const float limit = wmax >= kSplitLimit ? -1.f : fminf(kSplitLimit, 1.6e38f / ((float)terms * wmax));
   return as_float(__builtin_amdgcn_readfirstlane(as_uint(limit)));     // (a scalar register)
+}
+
+// The thread index, opaque to the compiler: what is derived from it is formed
+// where it is used, not kept in registers through the loops around it.
+__device__ __forceinline__ int fresh_tid() {
+  int x = threadIdx.x;
+  asm volatile("" : "+v"(x));
+  return x;
 }
 
 __device__ __forceinline__ floatx4 mfma_bf16(bf16x8 a, bf16x8 b, floatx4 c) {
@@ -408,10 +417,7 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
     }
   };
   auto list_chunk = [&](int first) __attribute__((always_inline)) {
-    // (opaque, so that nothing derived from it is kept in registers through the
-    // tile loop for the next chunk)
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
+    const int tid = fresh_tid();               // (nothing is kept through the tile loop for the next chunk)
     if constexpr (kFused) {
       total = list_tiles<INTS>([&](int l) { return l < L ? m.lcount[l] : N; }, L, N, lvl_lo, a.level_hi, group, Q, first,
                                kCap, tid, list, wsum, bad);
@@ -551,24 +557,28 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
     return r;
   };
 
-  // One gate row's sum over every column of tile row i, from the fp32 values.
-  auto fp32_sum = [&](const int *t, int i, int gate_row) __attribute__((always_inline)) -> float {
-    float sum = 0.f;
+  // This wave's partial sums of tile t on the fp32 matrix unit: the same columns,
+  // operands (all of them waited for) and weights from memory.
+  auto fp32_tile = [&](const int *t, float *cb) __attribute__((always_inline)) {
+    const int x0 = fresh_tid(), wave = x0 >> 6, i16 = x0 & 15, g4 = (x0 >> 4) & 3;
+    const int rslot = wave >> 2, rcol = D::KR * (wave & 3) + 4 * g4, xcol = D::KX * wave + 4 * g4;
+    const int xc = XS > 0 ? code(t, i16, 0) : -1, hc = code(t, i16, kDag ? 1 + rslot : rslot);
 #pragma unroll 1
-    for (int c = kHoisted ? H : 0; c < CODES * H; c += 4) {
-      const int src = code(t, i, c / H), o = c % H;
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (src >= 0) {
-        const uint32_t so = (uint32_t)(src * H + o) * 8u;
-        const u32x4 lo = hs.load2_at(so), hi = hs.load2_at(so + 16u);
-        v = make_float4(as_float(lo.x), as_float(lo.z), as_float(hi.x), as_float(hi.z));
-      } else if (src <= -2) {
-        v = as_float4(xin.load4((uint32_t)((-2 - src) * H + o) * 4u));
+    for (int nt = 0; nt < NT; ++nt) {
+      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int b = 0; b < 2 * (XS + RS); ++b) {             // 16 columns at a time
+        const bool in = b < 2 * XS;
+        const int o = in ? xcol + 16 * b : rcol + 16 * (b - 2 * XS), c = in ? xc : hc;
+        const uint32_t so = c >= 0 ? (uint32_t)(c * H + o) * 8u : kNoSource;
+        const u32x4 plain = xin.load4(c <= -2 ? (uint32_t)((-2 - c) * H + o) * 4u : kNoSource);
+        const float4 v = pick_block(c >= 0, hs.load2_at(so), hs.load2_at(so + 16u), plain);
+        const int wc = kDag ? (in ? o : H + rslot * H + o) : rslot * H + o;
+        acc = mfma_k16(v, weight_slice_at<CELL, H, J>(a, hbase, 16 * nt + i16, wc), acc);
       }
-      const float4 w4 = weight_slice_at<CELL, H, J>(a, hbase, gate_row, c);
-      sum = fmaf(v.x, w4.x, fmaf(v.y, w4.y, fmaf(v.z, w4.z, fmaf(v.w, w4.w, sum))));
+#pragma unroll
+      for (int v = 0; v < 4; ++v) cb[(wave * kTileM + 4 * g4 + v) * LDC + 16 * nt + i16] = acc[v];
     }
-    return sum;
   };
 
   for (int first = 0;; first += kCap) {
@@ -740,7 +750,12 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
         for (int v = 0; v < 4; ++v) cb[(wave * kTileM + 4 * g4 + v) * LDC + 16 * nt + i16] = hi[nt][v] + lo[nt][v];
       __syncthreads();
       CORTEX_TRACE_POINT(l, 3);
-      if (stop_s[e & 1]) return;             // a wave gave up its wait: every wave stops here
+      const int stop = stop_s[e & 1], mark = t[3];
+      if (stop) return;                      // a wave gave up its wait: every wave stops here
+      if (__builtin_expect(mark < 0, 0)) {   // (the same for every wave)
+        fp32_tile(t, cb);
+        __syncthreads();
+      }
       if (kOneBuffer || eside == (e & 1)) {
         // the eight partial sums in one order whatever J is, then the bias
         float z[PP][GATES];
@@ -761,13 +776,6 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
             z[p][g] = (kHoisted ? pv[p] : bias[g]) + q[0];
           }
         if constexpr (kOneBuffer) __syncthreads();     // the partial sums may be overwritten
-        if (__builtin_expect(t[3] < 0, 0)) {
-          // an operand or a weight cannot be split: the sums in plain fp32
-#pragma unroll
-          for (int p = 0; p < PP; ++p)
-#pragma unroll
-            for (int g = 0; g < GATES; ++g) z[p][g] = (kHoisted ? pv[p] : bias[g]) + fp32_sum(t, erow + D::RSTEP * p, g * J + ej);
-        }
         if constexpr (kLstm) {
           const int row = t[0] + erow;
           const float cn = sigmoidf(z[0][0]) * tanh_f(z[0][4]) + sigmoidf(z[0][1]) * as_float(cc[0].x) +
@@ -793,7 +801,8 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
 #pragma unroll
           for (int p = 0; p < PP; ++p) {
             const int row = t[0] + erow + D::RSTEP * p;
-            if (epart == 0 && row < t[1]) a.h[(size_t)row * H + hbase + ej] = hv[p];
+            // (a 32-bit byte offset: a 64-bit address per lane would be spilled)
+            if (epart == 0 && row < t[1]) *(float *)((char *)a.h + (uint32_t)(row * H + hbase + ej) * 4u) = hv[p];
           }
         }
       }
@@ -943,25 +952,13 @@ __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) 
     }
     return xi;
   };
-  // Plain fp32 dot products, for rows or weights that cannot be split: gate row
-  // m of segment sg (0: W with input row r, 1: U with staged row r).
-  auto fp32_dot = [&](int sg, int r, int gate_row) __attribute__((always_inline)) -> float {
-    float sum = 0.f;
-    if (r < 0) return sum;
-#pragma unroll 1
-    for (int c = 0; c < H; c += 4) {
-      float4 v;
-      if (sg == 1) {
-        const uint32_t so = (uint32_t)(r * H + c) * 8u;
-        const u32x4 lo = hs.load2_at(so), hi = hs.load2_at(so + 16u);
-        v = make_float4(as_float(lo.x), as_float(lo.z), as_float(hi.x), as_float(hi.z));
-      } else {
-        v = as_float4(xin.load4((uint32_t)(r * H + c) * 4u));
-      }
-      const float4 w4 = weight_slice_at<CELL, H, J>(a, hbase, gate_row, sg * H + c);
-      sum = fmaf(v.x, w4.x, fmaf(v.y, w4.y, fmaf(v.z, w4.z, fmaf(v.w, w4.w, sum))));
-    }
-    return sum;
+  // 16 columns from column c (this lane's four of them) of gate tile nt on the
+  // fp32 matrix unit: segment 0 is W, with input rows, 1 is U, with staged rows.
+  auto fp32_block = [&](int sg, int c, int row, const float4 v, floatx4 acc) __attribute__((always_inline)) -> floatx4 {
+    return mfma_k16(v, weight_slice_at<CELL, H, J>(a, hbase, row, sg * H + c), acc);
+  };
+  auto fp32_input = [&](int xr, int c) __attribute__((always_inline)) -> float4 {
+    return as_float4(xin.load4(xr >= 0 ? (uint32_t)(xr * H + c) * 4u : kNoSource));
   };
   // Tree sum of this thread's part of the eight partial sums at c0 (stride:
   // floats between waves), then over the parts of the pair: one order whatever J.
@@ -1011,6 +1008,14 @@ __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) 
           for (int b = 0; b < 2 * RS; ++b) xl[t][b] = xin.load4(o + 64u * b);
         }
       };
+      // this wave's partial sums of leaf tile t
+      auto leaf_sums = [&](int t, const floatx4 (&z)[NT]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+          if (16 * nt + i16 < 3 * J)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) C_s[(wave * LEAF + t * kTileM + 4 * g4 + v) * LDL + 16 * nt + i16] = z[nt][v];
+      };
       issue_leaf(0);
 #pragma unroll 1
       for (int n = 0; n < cnt; ++n) {
@@ -1029,16 +1034,31 @@ __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) 
             mfma_split<NT>(split8(v0, v1), w, hi, lo, [](auto) {});
           });
 #pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
-            if (16 * nt + i16 < 3 * J)
-#pragma unroll
-              for (int v = 0; v < 4; ++v)
-                C_s[(wave * LEAF + t * kTileM + 4 * g4 + v) * LDL + 16 * nt + i16] = hi[nt][v] + lo[nt][v];
+          for (int nt = 0; nt < NT; ++nt) hi[nt] += lo[nt];
+          leaf_sums(t, hi);
         }
         issue_leaf(n + 1);
         if (mx >= limit) big_s[n & 1] = 1;
         __syncthreads();
-        const bool big = big_s[n & 1] != 0;
+        if (__builtin_expect(big_s[n & 1] != 0, 0)) {
+          // (every wave) its partial sums again from the fp32 values
+          const int x0 = fresh_tid(), r16 = x0 & 15, c0 = D::KW * (x0 >> 6) + 4 * ((x0 >> 4) & 3);
+#pragma unroll 1
+          for (int t = 0; t < MT; ++t) {
+            const int xr = list[n * LEAF + t * kTileM + r16];
+            floatx4 acc[NT];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int b = 0; b < 2 * RS; ++b) {
+              const float4 v = fp32_input(xr, c0 + 16 * b);
+#pragma unroll
+              for (int nt = 0; nt < NT; ++nt) acc[nt] = fp32_block(0, c0 + 16 * b, 16 * nt + r16, v, acc[nt]);
+            }
+            leaf_sums(t, acc);
+          }
+          __syncthreads();
+        }
         if (tid < LEAF * J) {
           const int j = tid % J, i = tid / J, row = rowbase + i;
           float z[3];
@@ -1053,15 +1073,6 @@ __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) 
 #pragma unroll
               for (int k = 0; k < w / 2; ++k) q[k] = q[2 * k] + q[2 * k + 1];
             z[g] = bias_s[g * J + j] + q[0];
-          }
-          if (__builtin_expect(big, 0)) {
-#pragma unroll 1
-            for (int g = 0; g < 3; ++g) {
-              const float sum = bias_s[g * J + j] + fp32_dot(0, list[n * LEAF + i], g * J + j);
-              if (g == 0) z[0] = sum;
-              if (g == 1) z[1] = sum;
-              if (g == 2) z[2] = sum;
-            }
           }
           if (row < off1) {
             const float cn = sigmoidf(z[0]) * tanh_f(z[2]), hv = sigmoidf(z[1]) * tanh_f(cn);
@@ -1112,15 +1123,31 @@ __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) 
     }
   };
 
+  // This wave's partial sums of a tile: z of x and h~ (the last gate tile of x
+  // alone), f of each slot with the last gate tile.
+  auto tile_sums = [&](float *cb, const floatx4 (&z)[NT], const floatx4 (&f)[4][1]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      float *c0 = &cb[(wave * kTileM + 4 * g4 + v) * LDC];
+#pragma unroll
+      for (int nt = 0; nt < HT; ++nt) c0[16 * nt + i16] = z[nt][v];
+      const float x = z[NT - 1][v];
+      if (i16 < 16 - J) {
+        c0[D::UB + i16] = x + ((f[0][0][v] + f[1][0][v]) + (f[2][0][v] + f[3][0][v]));
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) c0[D::FB + k * J + i16 - (16 - J)] = x + f[k][0][v];
+      }
+    }
+  };
+
   int total = 0, listed = 0;
 #pragma unroll 1
   for (int first = 0;; first += kCap) {
     if (first > 0 && first >= total) break;
     __syncthreads();                          // every wave is done with the records (or the leaf inputs)
     {
-      // (opaque, so that nothing derived from it is kept through the tile loop)
-      int t0 = threadIdx.x;
-      asm volatile("" : "+v"(t0));
+      const int t0 = fresh_tid();
       total = list_tiles<INTS>([&](int l) { return a.level_offsets[l]; }, L, N, max(a.level_lo, 1), a.level_hi, group, Q, first,
                                kCap, t0, list, wsum, bad);
       listed = min(total - first, kCap);
@@ -1277,28 +1304,45 @@ __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) 
       CORTEX_TRACE_WAVE(l);
       float *cb = &C_s[(e & 1) * CBUF];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        float *c0 = &cb[(wave * kTileM + 4 * g4 + v) * LDC];
-#pragma unroll
-        for (int nt = 0; nt < HT; ++nt) c0[16 * nt + i16] = hi[nt][v] + lo[nt][v];
-        const float x = hi[NT - 1][v] + lo[NT - 1][v];
-        float f[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) f[k] = fh[k][0][v];
-        if (i16 < 16 - J) {
-          c0[D::UB + i16] = x + ((f[0] + f[1]) + (f[2] + f[3]));
-        } else {
-#pragma unroll
-          for (int k = 0; k < 4; ++k) c0[D::FB + k * J + i16 - (16 - J)] = x + f[k];
-        }
-      }
+      for (int nt = 0; nt < NT; ++nt) hi[nt] += lo[nt];
+      tile_sums(cb, hi, fh);
       // (the cells of the next tile go to the other half of the waves)
       if (more) issue_cells(tn, e + 1);
 #pragma unroll
       for (int k = 0; k < 4; ++k) cd[k] = cdn[k];
       __syncthreads();
       CORTEX_TRACE_POINT(l, 3);
-      if (stop_s[e & 1]) return;             // a wave gave up its wait: every wave stops here
+      const int stop = stop_s[e & 1], mark = t[3];
+      if (stop) return;                      // a wave gave up its wait: every wave stops here
+      if (__builtin_expect(mark < 0, 0)) {
+        // (every wave) its partial sums again from the fp32 values, all waited for
+        floatx4 z[NT], f[4][1];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) z[nt] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) f[k][0] = floatx4{0.f, 0.f, 0.f, 0.f};
+        const int x0 = fresh_tid(), r16 = x0 & 15, c0 = D::KW * (x0 >> 6) + 4 * ((x0 >> 4) & 3);
+#pragma unroll 1
+        for (int c = c0; c < c0 + D::KW; c += 16) {
+          const float4 x = fp32_input(code(t, r16, 4), c);
+          float4 h = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) z[nt] = fp32_block(0, c, 16 * nt + r16, x, z[nt]);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const int ch = code(t, r16, k);
+            const uint32_t so = ch >= 0 ? (uint32_t)(ch * H + c) * 8u : kNoSource;
+            const u32x4 lo = hs.load2_at(so), up = hs.load2_at(so + 16u);
+            const float4 v = make_float4(as_float(lo.x), as_float(lo.z), as_float(up.x), as_float(up.z));
+            h = make_float4(h.x + v.x, h.y + v.y, h.z + v.z, h.w + v.w);
+            f[k][0] = fp32_block(1, c, 16 * (NT - 1) + r16, v, f[k][0]);
+          }
+#pragma unroll
+          for (int nt = 0; nt < HT; ++nt) z[nt] = fp32_block(1, c, 16 * nt + r16, h, z[nt]);
+        }
+        tile_sums(cb, z, f);
+        __syncthreads();
+      }
       if (eside == (e & 1)) {
         const float *c0 = &cb[erow * LDC + ej];
         constexpr int WST = kTileM * LDC;
@@ -1307,29 +1351,6 @@ __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) 
         for (int g = 0; g < 3; ++g) z[g] = bias_s[g * J + ej] + sum_parts(c0 + g * J, WST);
 #pragma unroll
         for (int k = 0; k < 4; ++k) f[k] = bias_s[3 * J + ej] + sum_parts(c0 + D::FB + k * J, WST);
-        if (__builtin_expect(t[3] < 0, 0)) {
-          // an operand or a weight cannot be split: the sums in plain fp32
-          const int xr = code(t, erow, 4);
-#pragma unroll 1
-          for (int g = 0; g < 4; ++g) {
-            float sum = fp32_dot(0, xr, g * J + ej);
-            if (g == 3) f[0] = f[1] = f[2] = f[3] = sum;
-#pragma unroll 1
-            for (int k = 0; k < 4; ++k) {
-              const float d = fp32_dot(1, code(t, erow, k), g * J + ej);
-              sum += d;
-              if (g == 3) {
-                if (k == 0) f[0] = bias_s[3 * J + ej] + (f[0] + d);
-                if (k == 1) f[1] = bias_s[3 * J + ej] + (f[1] + d);
-                if (k == 2) f[2] = bias_s[3 * J + ej] + (f[2] + d);
-                if (k == 3) f[3] = bias_s[3 * J + ej] + (f[3] + d);
-              }
-            }
-            if (g == 0) z[0] = bias_s[0 * J + ej] + sum;
-            if (g == 1) z[1] = bias_s[1 * J + ej] + sum;
-            if (g == 2) z[2] = bias_s[2 * J + ej] + sum;
-          }
-        }
         float fc[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) fc[k] = (cmask >> k) & 1u ? sigmoidf(f[k]) * as_float(cc[k].x) : 0.f;
@@ -1411,14 +1432,6 @@ __global__ void __launch_bounds__(kFwdThreads) mvrnn_cols_kernel(FwdArgs a) {
   const InBuf xm(a.leaf_mat, a.leaf_mat ? (uint32_t)a.x_rows * D * D * 4 : 0u);
   const int side = wave >> 2, kk = 32 * (wave & 3) + 8 * g4;       // matrix (0: A, 1: B) and this lane's first row of it
   const int col = 16 * cb + i16;                                   // this lane's column of A, B and P
-  // (opaque: what is derived from it is formed where it is used, not kept in
-  // registers through the node loop)
-  auto fresh_tid = [&]() __attribute__((always_inline)) -> int {
-    int x = threadIdx.x;
-    asm volatile("" : "+v"(x));
-    return x;
-  };
-
   const int status0 = load_status(a.status);
   const int L = *a.num_levels;
   if (tid < 2) stop_s[tid] = 0;
@@ -1556,8 +1569,7 @@ __global__ void __launch_bounds__(kFwdThreads) mvrnn_cols_kernel(FwdArgs a) {
     if (first > 0 && first >= total) break;
     __syncthreads();                            // every wave is done with the records
     {
-      int t0 = threadIdx.x;
-      asm volatile("" : "+v"(t0));              // (nothing derived from it is kept through the node loop)
+      const int t0 = fresh_tid();
       total = list_tiles<INTS, 1>([&](int l) { return a.level_offsets[l]; }, L, N, 1, L, group, ngroups, first, kCap, t0, list,
                                   wsum, bad);
       listed = min(total - first, kCap);
@@ -1650,35 +1662,36 @@ __global__ void __launch_bounds__(kFwdThreads) mvrnn_cols_kernel(FwdArgs a) {
         for (int m = 0; m < HM; ++m) *(floatx4 *)&cbuf[(wave * 16 + i16) * LDN + 16 * (m0 + m) + 4 * g4] = hi[m] + lo[m];
       });
       __syncthreads();
-      const bool stop = stop_s[phase & 1] != 0;
+      const int stop = stop_s[phase & 1], mark = t[3];
       ++phase;
       if (stop) return;
+      if (__builtin_expect(mark < 0, 0)) {
+        // (every wave) its partial sums again on the fp32 matrix unit, operands
+        // (all waited for) and weights from memory: step k takes the rows
+        // 32 (wave & 3) + 8 g4 + k of this wave's matrix
+        const int x0 = fresh_tid(), wave = x0 >> 6, i16 = x0 & 15, g4 = (x0 >> 4) & 3;
+        const int c = t[4 + (wave >> 2)];
+        const uint32_t at = (uint32_t)(((c >= 0 ? c : -2 - c) * D + 32 * (wave & 3) + 8 * g4) * D + 16 * cb + i16);
+#pragma unroll 1
+        for (int m = 0; m < MT; ++m) {
+          floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+          for (int k = 0; k < 8; ++k) {
+            float x = 0.f;
+            if (c >= 0) x = as_float(ps.load1_at((at + k * D) * 8u).x);
+            else if (c <= -2) x = as_float(xm.load1((at + k * D) * 4u));
+            acc = mfma16x16x4(a.W_M[(size_t)(16 * m + i16) * 2 * D + 32 * wave + 8 * g4 + k], x, acc);
+          }
+          *(floatx4 *)&cbuf[(wave * 16 + i16) * LDN + 16 * m + 4 * g4] = acc;
+        }
+        __syncthreads();
+      }
       {
         const int x0 = fresh_tid(), n = x0 & 15, r4 = 4 * (x0 >> 4);
         floatx4 s[kFwdWaves];
 #pragma unroll
         for (int w = 0; w < kFwdWaves; ++w) s[w] = *(const floatx4 *)&cbuf[(w * 16 + n) * LDN + r4];
-        floatx4 sum = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
-        if (__builtin_expect(t[3] < 0, 0)) {
-          // an element or a weight cannot be split: the sums in plain fp32
-#pragma unroll 1
-          for (int i = 0; i < 4; ++i) {
-            float acc = 0.f;
-#pragma unroll 1
-            for (int k = 0; k < 2 * D; ++k) {
-              const int c = t[4 + k / D];
-              const uint32_t at = (uint32_t)(((c >= 0 ? c : -2 - c) * D + k % D) * D + 16 * cb + n);
-              float x = 0.f;
-              if (c >= 0) x = as_float(ps.load1_at(at * 8u).x);
-              else if (c <= -2) x = as_float(xm.load1(at * 4u));
-              acc = fmaf(a.W_M[(size_t)(r4 + i) * 2 * D + k], x, acc);
-            }
-            if (i == 0) sum.x = acc;
-            if (i == 1) sum.y = acc;
-            if (i == 2) sum.z = acc;
-            if (i == 3) sum.w = acc;
-          }
-        }
+        const floatx4 sum = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
         const uint32_t el = (uint32_t)(row * D * D + r4 * D + 16 * cb + n);
 #pragma unroll
         for (int i = 0; i < 4; ++i) ps.store1(el + i * D, sum[i], tag);
