@@ -219,12 +219,12 @@ int cortex_tree_forward(int32_t cell, int32_t H, const cortex_lin_t *lin, const 
  * Where the cell has a fused instance -- TreeRNN (H = 64 up to 320 nodes,
  * 256, 512), N-ary TreeLSTM (64; 256 up to 1,536 nodes), child-sum TreeLSTM
  * (64, 512; 256 below 1,200 nodes), the TreeGRU cells (64, 256, 512), MV-RNN
- * (d = 64); N <= 2048, the schedule knobs at their defaults
+ * (d = 64; 128 up to 47 nodes); N <= 2048, the schedule knobs at their defaults
  * (FWD_NODE_GROUPS aside) and the batch's linearization and structure
  * fitting one compute unit's LDS beside the kernel's own -- this is ONE
  * kernel launch: every workgroup linearizes the batch in LDS for itself (the
  * single-workgroup linearizer's algorithm) and workgroup 0 writes *lin out.
- * Otherwise (MV-RNN at d = 128, larger batches) it enqueues cortex_linearize,
+ * Otherwise (larger batches) it enqueues cortex_linearize,
  * then cortex_tree_forward.
  *   d_children  [N*K] int32 by node id, -1 = absent slot (as cortex_linearize)
  *   d_ws        cortex_tree_infer_workspace_bytes(cell, N, K, H) bytes of

@@ -2858,7 +2858,7 @@ static bool pick(int cell, int H, int32_t N, int32_t K, bool cached, Instance &o
     return true;
   }
   if (cell == CORTEX_MVRNN && H == MvCols::D) {
-    out.fn = mvrnn_cols_kernel;
+    out.fn = mvrnn_cols_kernel<false>;
     out.J = MvCols::RB;
     out.threads = kFwdThreads;
     out.lds = 0;
@@ -2913,6 +2913,14 @@ static bool pick_fused(int cell, int H, int32_t N, int32_t K, Instance &out) {
     out.J = MvDims<kMvD>::RB;
     out.threads = MvDims<kMvD>::kThreads;
     out.lds = mv_fused_ints<kMvD>(N) * sizeof(int);
+    return true;
+  }
+  if (cell == CORTEX_MVRNN && H == MvCols::D && K == 2 && N <= MvCols::kFusedRows) {
+    out.fn = mvrnn_cols_kernel<true>;
+    out.J = MvCols::RB;
+    out.threads = kFwdThreads;
+    out.lds = (N + small_lin_ints<kFwdThreads>(N, 2)) * sizeof(int);
+    out.uses_keep = true;
     return true;
   }
   const bool gru = cell == CORTEX_CHILDSUM_TREEGRU || cell == CORTEX_SIMPLE_TREEGRU;

@@ -1,6 +1,6 @@
 """cortex_tree_infer and cortex_dag_infer: linearization and forward in one call.  For the cells
 with a fused instance (TreeRNN, N-ary and child-sum TreeLSTM, TreeGRU cells,
-MV-RNN at d = 64, DAG-RNN with 16-unit slices)
+MV-RNN at d = 64 and small batches at d = 128, DAG-RNN with 16-unit slices)
 it is one launch in which every workgroup linearizes the batch itself;
 its linearization must be bit-exact and its states bitwise those of
 cortex_linearize followed by cortex_tree_forward (the same contraction in the
@@ -71,6 +71,10 @@ FUSED = {
     "treegru_h512_b2": lambda: I.childsum_treegru_workload(81, batch=2, H=512),
     "mvrnn_d64_b10": lambda: cached_workload(3, 0),
     "mvrnn_d64_ragged": lambda: I.mvrnn_workload(82, batch=4, d=64, leaf_lo=1, leaf_hi=30),
+    "mvrnn_d128_one_leaf": lambda: I.mvrnn_workload(86, batch=1, d=128, leaf_lo=1, leaf_hi=1),
+    "mvrnn_d128_one_pair": lambda: I.mvrnn_workload(87, batch=1, d=128, leaf_lo=2, leaf_hi=2),
+    "mvrnn_d128_ragged": lambda: I.mvrnn_workload(88, batch=4, d=128, leaf_lo=1, leaf_hi=6),
+    "mvrnn_d128_47": lambda: I.mvrnn_workload(89, batch=1, d=128, leaf_lo=24, leaf_hi=24),
     "dag_h256_10x10": lambda: I.paper_grid_workload("dagrnn", 1, "s"),
     "dag_h256_10x10_b10": lambda: I.paper_grid_workload("dagrnn", 10, "s"),
     "dag_h64_ragged": lambda: I.dagrnn_workload(83, n_grids=3, rows=7, cols=5, H=64),
@@ -148,7 +152,8 @@ def test_fused_launch_node_groups(groups):
 TWO_LAUNCH = {
     "tree_rnn_h64_over_320": (lambda: I.tree_rnn_workload(71, n_leaves=200, H=64), None),
     "tree_rnn_h64_unroll": (lambda: I.tree_rnn_workload(72, n_leaves=40, H=64), (C.CORTEX_KNOB_TREE_UNROLL, 2)),
-    # d = 128: [A; B] alone takes 129 KB of LDS, the linearization does not fit beside it
+    # d = 128: one launch up to 47 nodes
+    "mvrnn_d128_49": (lambda: I.mvrnn_workload(90, batch=1, d=128, leaf_lo=25, leaf_hi=25), None),
     "mvrnn_d128": (lambda: I.mvrnn_workload(73, batch=3, d=128), None),
     "treegru_h256_phase_barrier": (lambda: I.childsum_treegru_workload(74, batch=3, H=256),
                                    (C.CORTEX_KNOB_LEVEL_SYNC, 3)),

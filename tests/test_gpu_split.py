@@ -151,6 +151,19 @@ def test_mvrnn_node_groups(groups):
     compare_states(ref, O.forward_workload(wl), "mvrnn")
 
 
+@pytest.mark.parametrize("leaves,status", [(24, C.CORTEX_ST_INPUT_RANGE), (25, C.CORTEX_ST_OK)])
+def test_mvrnn_checks_input_indexes(leaves, status):
+    """cortex_tree_infer up to 47 nodes refuses an input index out of range at
+    any node; beyond, MV-RNN reads them at leaves only."""
+    wl = I.mvrnn_workload(46, batch=1, d=128, leaf_lo=leaves, leaf_hi=leaves)
+    x_index = wl.x_index.copy()
+    x_index[np.nonzero(x_index < 0)[0][0]] = leaves                 # an inner node; the table has `leaves` rows
+    announce("split mvrnn x_index N=%d" % wl.N)
+    dw = DeviceWorkload(dataclasses.replace(wl, x_index=x_index))
+    dw.infer()
+    assert dw.status_code() == status
+
+
 UNSPLITTABLE = {
     # (one level: P is linear, and deeper products of huge finite values leave the fp32 range)
     "mvrnn": lambda: I.mvrnn_workload(32, batch=9, d=128, leaf_lo=2, leaf_hi=2),
