@@ -1410,6 +1410,7 @@ struct MvCols {
   static constexpr int INTS = 6;                         // node record: row, level end, level, level start / -1, two codes
   static constexpr int kCap = 512, kFusedCap = 32;       // records held at a time
   static constexpr int kFusedRows = 47;                  // one launch, and every node's input index checked, up to here
+  static constexpr int kCheckRows = 640;                 // every entry of child_rows checked up to here
   static constexpr size_t kXchg = (size_t)RB * 2 * D;    // published partial sums per node
 };
 
@@ -1599,6 +1600,14 @@ __global__ void __launch_bounds__(kFwdThreads) mvrnn_cols_kernel(FwdArgs a) {
     return false;
   };
 
+  if (!kFused && N <= M::kCheckRows) {
+    // small batches: every child row is in range, also those no node reads
+#pragma unroll 1
+    for (int i = blockIdx.x * kFwdThreads + fresh_tid(); i < 2 * N; i += gridDim.x * kFwdThreads) {
+      const int c = a.child_rows[i];
+      if (c < -1 || c >= N) raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
+    }
+  }
   int total = 0, listed = 0, off1 = 0;
 #pragma unroll 1
   for (int first = 0;; first += kCap) {

@@ -151,6 +151,21 @@ def test_mvrnn_node_groups(groups):
     compare_states(ref, O.forward_workload(wl), "mvrnn")
 
 
+@pytest.mark.parametrize("leaves,value,status", [
+    (320, "N", C.CORTEX_ST_BAD_LINEARIZATION), (320, -2, C.CORTEX_ST_BAD_LINEARIZATION), (2, "N", C.CORTEX_ST_BAD_LINEARIZATION),
+    (320, 0, C.CORTEX_ST_OK), (321, "N", C.CORTEX_ST_OK)])
+def test_mvrnn_checks_child_rows(leaves, value, status):
+    """Up to 640 nodes every entry of child_rows has to be a row or -1, also
+    those of leaf rows, which no node reads."""
+    wl = I.mvrnn_workload(45, batch=1, d=128, leaf_lo=leaves, leaf_hi=leaves)
+    announce("split mvrnn child_rows N=%d %s" % (wl.N, value))
+    dw = DeviceWorkload(wl)
+    dw.linearize()
+    dw.lin.child_rows[2] = wl.N if value == "N" else value          # row 1 is a leaf
+    dw.forward()
+    assert dw.status_code() == status
+
+
 @pytest.mark.parametrize("leaves,status", [(24, C.CORTEX_ST_INPUT_RANGE), (25, C.CORTEX_ST_OK)])
 def test_mvrnn_checks_input_indexes(leaves, status):
     """cortex_tree_infer up to 47 nodes refuses an input index out of range at
