@@ -87,6 +87,7 @@ def bound_of(flops, byts):
 
 
 FORWARD_SOURCES = ("paper_2011_01383_amd/csrc/forward.hip", "paper_2011_01383_amd/csrc/forward_split.hpp",
+                   "paper_2011_01383_amd/csrc/slice_forward_body.hpp",
                    "paper_2011_01383_amd/csrc/cortex_device.hpp",
                    "paper_2011_01383_amd/csrc/cortex_host.hpp", "paper_2011_01383_amd/csrc/lin_small.hpp")
 

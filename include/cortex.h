@@ -309,7 +309,8 @@ int cortex_dag_infer(int32_t H, const int32_t *d_children, const cortex_lin_t *l
  * Launch knobs, process-wide, read at each launch.  They change the schedule,
  * not what is computed: outputs are bitwise those of the defaults, except where
  * a knob picks a kernel that adds partial sums in another order (DAG-RNN slice
- * width, TREE_UNROLL = 1), whose states agree to rounding.
+ * width, TREE_UNROLL = 1, node groups other than 0 on a deep batch with few rows
+ * per level), whose states agree to rounding.
  *   CORTEX_KNOB_LIN_BLOCKS          workgroups of the linearizer (0 = chosen from N)
  *   CORTEX_KNOB_FWD_NODE_GROUPS     node groups of the forward; workgroups =
  *                                   hidden slices x node groups (0 = fill the

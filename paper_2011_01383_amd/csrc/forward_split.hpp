@@ -215,6 +215,36 @@ __device__ __forceinline__ int list_tiles(const Off &off, int L, int N, int lo, 
   return total;
 }
 
+// Deep, narrow batches.  A level that gives every group one tile at most costs
+// the exchange and that tile, and the fp32 kernels' tile is the shorter one by 0.2
+// to 0.7 us: its operands need no splitting, and the narrower slices have less
+// epilogue.  The level count is known on the device only, so the split kernels
+// hold the fp32 form as well and take it, every workgroup alike, where the levels
+// above the leaves have fewer than `rows` rows on average, or fewer than `even` and
+// the lowest of them less than twice the average (chains: in random trees it has
+// four times the average or more, and that is where the split kernels gain).
+//
+// us per step, split / fp32 form, at rows per level:
+//   N-ary TreeLSTM     16 918 / 824, 32 490 / 453, 41 (random) 105 / 115, 64 195 / 257
+//   TreeRNN 256        J = 16: 32 202 / 191, 58 (random) 98 / 108, 64 142 / 137,
+//                      96 91 / 96; J = 64: 64 239 / 203, 128 146 / 141, 130 (random)
+//                      138 / 158, 192 125 / 135
+//   TreeRNN 512        16 520 / 431, 58 (random) 163 / 174, 64 243 / 222, 96 256 / 256,
+//                      128 136 / 150
+//   child-sum          16 580 / 528, 32 378 / 366, 48 343 / 349, 64 345 / 433;
+//                      linearization in LDS: 48 170 / 155, 60 (random) 111 / 121,
+//                      64 147 / 141, 96 91 / 109
+struct NarrowRule {
+  int rows, even;
+};
+// off1, off2: first rows of levels 1 and 2.  (A scalar, and no branches: the rest
+// of the kernel must stay in uniform control flow.)
+__device__ __forceinline__ bool narrow_levels(int off1, int off2, int N, int L, NarrowRule r) {
+  const int64_t above = L - 1, inner = N - off1, lowest = off2 - off1;
+  const int narrow = (L > 1) & ((inner < r.rows * above) | ((inner < r.even * above) & (lowest * above < 2 * inner)));
+  return __builtin_amdgcn_readfirstlane(narrow) != 0;
+}
+
 // ---------------------------------------------------------------------------
 // TreeRNN, N-ary TreeLSTM and DAG-RNN at H = 256 and 512.
 //
@@ -260,6 +290,8 @@ struct SplitDims {
   static constexpr int PP = kPairs > ET ? kPairs / ET : 1;            // pairs per epilogue thread
   static constexpr int RSTEP = J == 64 ? ET / 64 : 4;                 // rows between a thread's pairs
   static constexpr int PARTS = kPairs < 256 ? 256 / kPairs : 1;       // threads per pair
+  static constexpr NarrowRule kNarrowRule = CELL == CORTEX_NARY_TREELSTM ? NarrowRule{36, 36}
+                                            : J == 64 ? NarrowRule{64, 150} : J == 32 ? NarrowRule{40, 100} : NarrowRule{40, 72};
   static_assert(KR % 32 == 0 && (!kDag || KX % 32 == 0) && 4 * KR == H, "whole 32-column steps, one child slot per wave");
   static_assert(PARTS <= 8 && H % J == 0 && J <= 64, "epilogue mapping");
 };
@@ -270,9 +302,20 @@ template <int CODES>
 constexpr size_t split_list_bytes(int cap) { return (size_t)cap * TileList<CODES>::kInts * sizeof(int); }
 constexpr int kSplitCap = 128, kSplitFusedCap = 48;
 
+// The kernel's arguments read again from the kernel argument segment, for a branch
+// that shares nothing with the rest of the kernel: no argument register has to
+// live across both (the LSTM cells; TreeRNN, with fewer, spills more scalars so).
+__device__ __forceinline__ FwdArgs fresh_args() {
+  typedef const __attribute__((address_space(4))) FwdArgs *Ptr;
+  Ptr p = (Ptr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const FwdArgs *)p;
+}
+
 // kHoisted (ablation, DAG-RNN with 64 units): W x + b of every row is read from
-// a.pre instead of being contracted here.
-template <int CELL, int H, int J, bool kFused, bool kWeightsFromMemory = false, bool kHoisted = false>
+// a.pre instead of being contracted here.  kNarrow: holds the form for deep, narrow
+// batches, with the linearization in LDS (2) or not (1).
+template <int CELL, int H, int J, bool kFused, bool kWeightsFromMemory = false, bool kHoisted = false, int kNarrow = 0>
 __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
   using D = SplitDims<CELL, H, J, kHoisted>;
   using TL = TileList<D::CODES>;
@@ -284,7 +327,10 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
 
   constexpr bool kWxLds = D::kWxLds, kOneBuffer = D::ET == 512;
   constexpr int WXP = XS * NT * kFwdThreads;    // one plane of the input weights, [step][tile][thread]
-  __shared__ __attribute__((aligned(16))) float C_s[(kOneBuffer ? 1 : 2) * CBUF];
+  constexpr int CS = (kOneBuffer ? 1 : 2) * CBUF;
+  typedef SliceLds<CELL, H, Cell<CELL, H>::J> NarrowLds;
+  constexpr int kPool = kNarrow && sizeof(NarrowLds) > CS * sizeof(float) ? (int)(sizeof(NarrowLds) + 3) / 4 : CS;
+  __shared__ __attribute__((aligned(16))) float C_s[kPool];
   __shared__ u32x4 Wx_s[kWxLds ? 3 * WXP : 1];
   __shared__ int wsum[kFwdWaves + 1];
   __shared__ int stop_s[2];
@@ -310,6 +356,13 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
 
   CORTEX_TRACE_KERNEL(0);
   const int status0 = load_status(a.status);
+  // (before the weights: which form of the kernel runs is known when they are still on their way)
+  int L = 0, off1 = 0, off2 = 0;
+  if constexpr (!kFused) {
+    L = *a.num_levels;
+    off1 = a.level_offsets[1];
+    if constexpr (kNarrow) off2 = a.level_offsets[N > 1 ? 2 : 1];
+  }
   if (tid < 2) stop_s[tid] = 0;
 
   // ---- weights: fragment (step s, tile nt) = gate row 16 nt + i16, two
@@ -349,7 +402,7 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
   };
 
   // ---- structure: the group's tiles and their operand sources ----
-  int L = 0, bad = 0, total = 0, listed = 0, off1 = 0;
+  int bad = 0, total = 0, listed = 0;
   SmallLin m;
   int *xnode = dyn + kCap * INTS;               // fused: the input row by node id
   auto row_of_slot = [&](int idx) __attribute__((always_inline)) -> int {
@@ -476,13 +529,20 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
     CORTEX_TRACE_KERNEL(10);
     if (status0 != 0) return;
   } else {
-    L = *a.num_levels;
     if (status0 != 0) return;
     if (L < 1 || L > N) {
       raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
       return;
     }
-    off1 = a.level_offsets[1];
+    if constexpr (kNarrow) {
+      static_assert(kLeafInputs && !kWeightsFromMemory, "leaf-input cells");
+      if (a.narrow_q > 0 && narrow_levels(off1, off2, N, L, D::kNarrowRule)) {
+        NarrowLds &n = *(NarrowLds *)C_s;
+        const FwdArgs b = kLstm ? fresh_args() : a;
+        slice_forward<CELL, H, Cell<CELL, H>::J, kNarrow == 2>(b, b.narrow_q, n.W_s, n.C_s, n.Z_s, n.bias_s, n.chunk, dyn);
+        return;
+      }
+    }
   }
   if constexpr (!kWeightsFromMemory) {
     split_weights(wv);
@@ -588,7 +648,7 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
     }
     list_chunk(first);
     if (!kFused && first == 0) {
-      if (kLeafInputs && !bad && (size_t)(4 * N + 1) * sizeof(int) <= kStructCacheBudget) {
+      if (kLstm && !bad && (size_t)(4 * N + 1) * sizeof(int) <= kStructCacheBudget) {
         // small batches: every row and input index is checked, also those that
         // no tile reads
 #pragma unroll 1
@@ -723,7 +783,7 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
       }
       CORTEX_TRACE_POINT(l, 2);
       {
-        const int cdn = more ? code(tn, i16, kDag ? 1 + rslot : rslot) : -1;
+        const int ft = fresh_tid(), cdn = more ? code(tn, ft & 15, (kDag ? 1 : 0) + (ft >> 8)) : -1;     // (row i16, slot rslot)
         const uint32_t so = staged_off(cdn), po = plain_off(cdn);
         if (more) issue_cells(tn, e + 1);        // (for the other half's epilogue: not this tile's)
         // the next tile's operands are requested between a step's products, into the
@@ -792,17 +852,17 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
           float hv[PP];
 #pragma unroll
           for (int p = 0; p < PP; ++p) hv[p] = tanh_f(z[p][0]);
+          const int unit = hbase + (fresh_tid() & (J - 1));     // (hbase + ej: not an address kept, and spilled, through the loop)
           // the tagged pairs (what the next level waits for) first, then the outputs
 #pragma unroll
           for (int p = 0; p < PP; ++p) {
             const int row = t[0] + erow + D::RSTEP * p;
-            if (epart == 0 && row < t[1]) hs.store1((uint32_t)(row * H + hbase + ej), hv[p], tag);
+            if (epart == 0 && row < t[1]) hs.store1((uint32_t)(row * H + unit), hv[p], tag);
           }
 #pragma unroll
           for (int p = 0; p < PP; ++p) {
             const int row = t[0] + erow + D::RSTEP * p;
-            // (a 32-bit byte offset: a 64-bit address per lane would be spilled)
-            if (epart == 0 && row < t[1]) *(float *)((char *)a.h + (uint32_t)(row * H + hbase + ej) * 4u) = hv[p];
+            if (epart == 0 && row < t[1]) *(float *)((char *)a.h + (uint32_t)(row * H + unit) * 4u) = hv[p];
           }
         }
       }
@@ -851,9 +911,12 @@ struct ChildsumSplit {
   // the split input weights, in LDS: [step][tile][plane][wave][lane] x 16 bytes
   static constexpr int kWx = RS * NT * 3 * kFwdThreads;
   static constexpr int kCap = 64;
+  static constexpr NarrowRule kNarrowRule = {40, 40}, kNarrowCachedRule = {40, 72};
   static_assert(J % 4 == 0 && J <= 8 && KW % 32 == 0 && kFwdWaves * LEAF * LDL <= 2 * CBUF, "tiling");
 };
 
+// kNarrowCached: the form for deep, narrow batches keeps the linearization in LDS.
+template <bool kNarrowCached>
 __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) {
   using D = ChildsumSplit;
   constexpr int CELL = CORTEX_CHILDSUM_TREELSTM, H = D::H, J = D::J;
@@ -883,6 +946,7 @@ __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) 
 
   CORTEX_TRACE_KERNEL(0);
   const int status0 = load_status(a.status);
+  const int L = *a.num_levels, off1 = a.level_offsets[1], off2 = a.level_offsets[N > 1 ? 2 : 1];   // (before the weights, as in slice_split_kernel)
   if (tid < 2) stop_s[tid] = big_s[tid] = 0;
 
   auto wfrag = [&](int sg, int s, int nt, int half) __attribute__((always_inline)) -> float4 {
@@ -900,15 +964,16 @@ __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) 
   if (tid < 4 * J) bias_s[tid] = a.b[childsum_gate(tid / J) * H + hbase + tid % J];     // i, o, u, f
 
   int bad = 0;
-  const int L = *a.num_levels;
   if (status0 != 0) return;
-  if (L < 1 || L > N) {
+  if (L < 1 || L > N || off1 < 1 || off1 > N) {
     raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
     return;
   }
-  const int off1 = a.level_offsets[1];
-  if (off1 < 1 || off1 > N) {
-    raise_status(a.status, CORTEX_ST_BAD_LINEARIZATION);
+  if (a.narrow_q > 0 && narrow_levels(off1, off2, N, L, kNarrowCached ? D::kNarrowCachedRule : D::kNarrowRule)) {
+    ChildsumLds<H> &n = *(ChildsumLds<H> *)C_s;
+    static_assert(sizeof(ChildsumLds<H>) <= sizeof(C_s), "the fp32 form's arrays take the place of the partial sums");
+    const FwdArgs b = fresh_args();
+    childsum_forward<H, kNarrowCached>(b, b.narrow_q, n.W_s, n.Cx, n.Ce, n.Z_s, n.bias_s, n.chunk, dyn);
     return;
   }
   Split8 wu[RS][NT];

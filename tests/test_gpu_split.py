@@ -151,6 +151,100 @@ def test_mvrnn_node_groups(groups):
     compare_states(ref, O.forward_workload(wl), "mvrnn")
 
 
+def _binary(wl, trees):
+    """The workload's cell, weights and inputs over other binary trees."""
+    children, is_leaf = I.forest_to_children(trees, 2)
+    rows = wl.x_table.shape[0]
+    x_index = np.full(is_leaf.size, -1, dtype=np.int32)
+    x_index[is_leaf] = np.arange(int(is_leaf.sum())) % rows
+    return dataclasses.replace(wl, children=children, x_index=x_index)
+
+
+def _childsum_trees(trees):
+    wl = childsum(47, 1, 9, 9)
+    children, is_leaf = I.forest_to_children(trees, 4)
+    return dataclasses.replace(wl, children=children, x_index=(np.arange(is_leaf.size) % 1000).astype(np.int32))
+
+
+def _cats(n, leaves):
+    return [I.caterpillar(leaves, left_spine=bool(i & 1)) for i in range(n)]
+
+
+def _chains(n, nodes):
+    out = []
+    for _ in range(n):
+        t = []
+        for _ in range(nodes - 1):
+            t = [t]
+        out.append(t)
+    return out
+
+
+# batches with few rows per level, for every kernel that holds the form for them,
+# and what CORTEX_KNOB_FWD_NODE_GROUPS makes of the same grid in the wide form
+DEEP = {
+    "nary_in_lds": (lambda: _binary(I.nary_treelstm_workload(48, batch=1, H=256), _cats(3, 400)), 8),
+    "nary": (lambda: _binary(I.nary_treelstm_workload(49, batch=1, H=256), _cats(2, 900)), 8),
+    "tree_rnn_h256": (lambda: _binary(I.tree_rnn_workload(50, n_leaves=64, H=256), _cats(3, 500)), 16),
+    "tree_rnn_h256_wide": (lambda: _binary(I.tree_rnn_workload(51, n_leaves=64, H=256), _cats(17, 200)), 64),
+    "tree_rnn_h512": (lambda: _binary(I.tree_rnn_workload(52, n_leaves=64, H=512), _cats(17, 90)), 16),
+    "childsum_in_lds": (lambda: _childsum_trees(_chains(3, 500)), 8),
+    "childsum": (lambda: _childsum_trees(_chains(2, 900)), 8),
+}
+
+
+def _best_us(dw, repeats=7):
+    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    best = float("inf")
+    for _ in range(repeats):
+        start.record()
+        dw.step()
+        end.record()
+        torch.cuda.synchronize()
+        best = min(best, start.elapsed_time(end))
+    assert dw.status_code() == 0
+    return 1e3 * best
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("name", sorted(DEEP))
+def test_deep_narrow_batches(name, mode):
+    """Deep, narrow batches take the form with the shorter tile: its states are
+    the oracle's under every level ordering, bitwise the same."""
+    wl = DEEP[name][0]()
+    announce("split deep %s mode %d N=%d" % (name, mode, wl.N))
+    C.cortex_set_knob(C.CORTEX_KNOB_LEVEL_SYNC, mode)
+    try:
+        got = run(wl).states_by_node()
+    finally:
+        C.cortex_set_knob(C.CORTEX_KNOB_LEVEL_SYNC, 0)
+    if mode == 0:
+        compare_states(got, O.forward_workload(wl), name)
+    else:
+        ref = run(wl).states_by_node()
+        for key in ref:
+            assert np.array_equal(ref[key], got[key]), key
+
+
+@pytest.mark.parametrize("name", sorted(DEEP))
+def test_deep_narrow_batches_are_faster(name):
+    """...and it is the faster one there: the same grid held to the wide form
+    (by its node groups) takes 1.07 to 1.4 times as long."""
+    wl, groups = DEEP[name][0](), DEEP[name][1]
+    announce("split deep times %s N=%d" % (name, wl.N))
+    dw = run(wl)
+    us = _best_us(dw)
+    grid = C.cortex_last_grid(1)
+    C.cortex_set_knob(C.CORTEX_KNOB_FWD_NODE_GROUPS, groups)
+    try:
+        dw.step()
+        assert C.cortex_last_grid(1) == grid
+        wide = _best_us(dw)
+    finally:
+        C.cortex_set_knob(C.CORTEX_KNOB_FWD_NODE_GROUPS, 0)
+    assert us < wide, (us, wide)
+
+
 @pytest.mark.parametrize("leaves,value,status", [
     (320, "N", C.CORTEX_ST_BAD_LINEARIZATION), (320, -2, C.CORTEX_ST_BAD_LINEARIZATION), (2, "N", C.CORTEX_ST_BAD_LINEARIZATION),
     (320, 0, C.CORTEX_ST_OK), (321, "N", C.CORTEX_ST_OK)])
