@@ -1,12 +1,15 @@
 // Forward kernels that contract on the bf16 matrix units with fp32 accuracy.
 //
 // Every fp32 operand x is split into three bf16 planes, x = p0 + p1 + p2 (each
-// the round-to-nearest bf16 of what the planes before it leave: exact for
-// normal values, 3 x 8 significant bits), and a product a*b is taken as the six
+// the round-to-nearest bf16 of what the planes before it leave: 3 x 8 significant
+// bits, exact from |x| of about 2^-110; below, the third plane meets the end of
+// bf16's range and up to 2^-134 is lost), and a product a*b is taken as the six
 // plane products of order 2^-16 and above,
 //   a0 b0  +  (a0 b1 + a1 b0 + a1 b1 + a0 b2 + a2 b0),
-// the first in an accumulator of its own.  The dropped terms are below 2^-26 of
-// |a b|, less than one fp32 rounding.  A 16x16x32 bf16 MFMA takes 16 cycles, so
+// the first in an accumulator of its own.  The dropped terms, a1 b2 + a2 b1 + a2 b2,
+// reach 2^-24 of |a b| at worst (a = b = 1.0039: 2^-24.01) and pass 2^-26 for 3.6%
+// of N(0,1) x U(-0.05, 0.05) products: about one fp32 rounding of the product, as
+// every fp32 multiplication makes.  A 16x16x32 bf16 MFMA takes 16 cycles, so
 // 32 k cost 96 cycles against 256 on the fp32 MFMA (8 x 32), and the sums are
 // closer to the exact ones: against 64 bits, dot products of N(0,1) rows with
 // U(-0.05, 0.05) weights are off by 0.47e-7 / 0.84e-7 / 1.75e-7 (2-norm,
@@ -1747,7 +1750,10 @@ __global__ void __launch_bounds__(kFwdThreads) mvrnn_cols_kernel(FwdArgs a) {
           xs.store1((uint32_t)((row * RB + cb) * 2 * D + (side ^ 1) * D + kk + (i16 >> 1)), q[0], tag);
       }
       const float4 v0 = make_float4(v[0], v[1], v[2], v[3]), v1 = make_float4(v[4], v[5], v[6], v[7]);
-      if (max_abs(max_abs(0.f, v0), v1) >= limit_s[wave]) t[3] = -1;     // read after the barrier
+      // (also where a lane's elements are all below 2^-100: P is linear, and its
+      // columns keep their own relative accuracy)
+      const float top = max_abs(max_abs(0.f, v0), v1);
+      if (top >= limit_s[wave] || as_uint(top) - 1u < as_uint(0x1p-100f) - 1u) t[3] = -1;     // read after the barrier
       const Split8 b = split8(v0, v1);
       // lane (column i16) receives rows 16 m + 4 g4 .. + 3; half of the row tiles
       // at a time, so the accumulators leave room for the next node's operands

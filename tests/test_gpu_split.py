@@ -315,6 +315,23 @@ def test_unsplittable_values(name, where, value):
         assert float(np.abs(got[key][fine] - r32[fine]).max()) <= 1e-4 * max(1.0, float(np.abs(r32[fine]).max())), key
 
 
+def test_mvrnn_tiny_matrices():
+    """P is linear in the children's matrices, so a column of tiny elements gives
+    a column of P with its own relative accuracy: elements of 1e-35, where three
+    bf16 planes hold 18 bits, leave an error of fp32 size (1e-6; with the planes it
+    is 2.8e-6)."""
+    wl = I.mvrnn_workload(53, batch=30, d=128, leaf_lo=2, leaf_hi=2)
+    wl = dataclasses.replace(wl, leaf_mat=np.ascontiguousarray(np.random.default_rng(53).normal(size=wl.leaf_mat.shape)
+                                                               .astype(np.float32)))
+    wl.leaf_mat[:, :, 70] *= np.float32(1e-35)
+    announce("split mvrnn tiny N=%d" % wl.N)
+    got, ref = run(wl).states_by_node()["P"], O.forward_workload(wl)["P"]
+    inner = wl.x_index < 0
+    for col in (69, 70, 71):
+        g, r = got[inner][:, :, col], ref[inner][:, :, col]
+        assert np.linalg.norm(g - r) <= 1e-6 * np.linalg.norm(r), col
+
+
 MANY = {
     "nary": lambda: I.nary_treelstm_workload(36, batch=100, H=256),
     "childsum": lambda: childsum(37, 100, 20, 80),
