@@ -108,9 +108,14 @@ def test_small_ragged(name, seed, groups):
     compare_states(dw.states_by_node(), O.forward_workload(wl), name)
 
 
-# Batches whose linearization does not fit the LDS structure cache: the
-# kernels then stage each chunk of tiles' structure from global memory.
+# Batches whose linearization does not fit the LDS structure cache: the fp32
+# kernels then stage each chunk of tiles' structure from global memory, the split
+# kernels (H = 256, random trees) list it per chunk of tiles.
 LARGE = {
+    "nary_h64": lambda: I.nary_treelstm_workload(38, batch=70, H=64),
+    "childsum_h64": lambda: I.childsum_treelstm_workload(39, batch=60, H=64),
+    "dag_h64": lambda: I.dagrnn_workload(40, n_grids=5, rows=23, cols=27, H=64),
+    "dag_h64_chains": lambda: I.dagrnn_workload(41, n_grids=3, rows=1, cols=901, H=64),
     "tree_rnn_h256": lambda: I.tree_rnn_workload(31, n_leaves=1800, H=256),
     "nary_h256": lambda: I.nary_treelstm_workload(32, batch=120, H=256),
     "childsum_h256": lambda: I.childsum_treelstm_workload(33, batch=110, H=256),
@@ -119,12 +124,12 @@ LARGE = {
 }
 
 
-def test_mvrnn_d128_uncached_structure():
-    """MV-RNN at d = 128 caches the structure in LDS only up to 640 rows
-    ([A;B] takes 129 KB there): a batch of 40 trees runs uncached."""
+def test_mvrnn_d128_many_trees():
+    """MV-RNN at d = 128 over 40 trees: every one of the 32 node groups has
+    several nodes on the low levels and none on the top ones."""
     wl = I.mvrnn_workload(37, batch=40, d=128)
     assert wl.N > 640
-    announce("uncached structure mvrnn d128 N=%d" % wl.N)
+    announce("mvrnn d128 N=%d" % wl.N)
     dw = run(wl)
     compare_states(dw.states_by_node(), O.forward_workload(wl), wl.name)
 
@@ -132,7 +137,8 @@ def test_mvrnn_d128_uncached_structure():
 @pytest.mark.parametrize("name", sorted(LARGE))
 def test_uncached_structure(name):
     wl = LARGE[name]()
-    assert wl.N > (2600 if wl.H < 512 else 1710), "must exceed the structure cache"
+    childsum_like = "childsum" in name or "treegru" in name
+    assert wl.N > (1706 if childsum_like else 2560), "must exceed the structure cache"
     announce("uncached structure %s N=%d" % (name, wl.N))
     dw = run(wl)
     compare_states(dw.states_by_node(), O.forward_workload(wl), name)
@@ -253,8 +259,8 @@ def test_host_errors_enqueue_nothing():
 
 @pytest.mark.parametrize("units,groups", [(64, 0), (64, 8), (64, 5), (16, 0), (16, 2), (0, 0)])
 def test_dag_slice_widths(units, groups):
-    """DAG-RNN at H = 256 under both slice widths (64 and 16 units; 0 = the
-    size-based default, 16 units at this size) and grids that do (multiples
+    """DAG-RNN at H = 256 under the slice widths that the knob forces (64 and
+    16 units; 0 = the size-based default, 16 units at this size) and grids that do (multiples
     of 32 workgroups) and do not use the XCD-grouped block order; each
     against the oracle."""
     wl = I.dagrnn_workload(77, n_grids=5, rows=13, cols=9, H=256)
@@ -267,41 +273,38 @@ def test_dag_slice_widths(units, groups):
 
 
 @pytest.mark.parametrize("groups", [2, 3])
-def test_dag_two_tile_steps_ragged(groups):
-    """64-unit DAG-RNN slices with few node groups, so most steps carry two
-    tiles (tile 1's child fragments are requested during tile 0's recurrent
-    part and waited for on their own) and levels end in ragged tiles; ten
-    20x15 grids, against the oracle."""
+def test_dag_several_tiles_per_level_ragged(groups):
+    """64-unit DAG-RNN slices with few node groups, so a group has several
+    tiles on most levels, one after another through the one buffer of partial
+    sums, the next one's operands requested during the last, and levels end
+    in ragged tiles; ten 20x15 grids, against the oracle."""
     wl = I.dagrnn_workload(79 + groups, n_grids=10, rows=20, cols=15, H=256)
-    announce("dag two-tile steps groups %d N=%d" % (groups, wl.N))
+    announce("dag several tiles groups %d N=%d" % (groups, wl.N))
     C.cortex_set_knob(C.CORTEX_KNOB_FWD_SLICE_UNITS, 64)
     dw = run(wl, groups)
     assert C.cortex_last_grid(1) == 4 * groups
-    compare_states(dw.states_by_node(), O.forward_workload(wl), "dag two-tile groups %d" % groups)
+    compare_states(dw.states_by_node(), O.forward_workload(wl), "dag several tiles groups %d" % groups)
 
 
 @pytest.mark.parametrize("groups,n_grids,side", [(16, 8, 24), (64, 3, 20), (2, 6, 32), (5, 4, 12)])
-def test_dag_half_steps(groups, n_grids, side):
-    """Levels of at most groups/2 tiles run as half steps (two groups per
-    tile, 32 units each): 8 grids of 24x24 over 16 groups mix half levels
-    (up to 128 rows) with whole ones, so groups change kind of step at
-    either parity of their step lists; 3 grids of 20x20 over 64 groups are
-    half steps throughout; 2 groups over 6 grids of 32x32 overflow the step
-    list, so the half steps of the one-tile levels fall in its first and
-    last chunks;
-    an odd group count (5) never splits.  Ragged tiles throughout; against
-    the oracle."""
+def test_dag_levels_and_groups(groups, n_grids, side):
+    """64-unit DAG-RNN slices over levels with fewer tiles than groups and
+    with more: 8 grids of 24x24 over 16 groups (at most 12 tiles a level:
+    groups skip levels); 3 grids of 20x20 over 64 groups (most groups idle);
+    2 groups over 6 grids of 32x32 (more tiles than the 128 the list holds,
+    with one-tile levels in its first and last chunks); 5 groups over 4 grids
+    of 12x12.  Ragged tiles throughout; against the oracle."""
     wl = I.dagrnn_workload(90 + groups, n_grids=n_grids, rows=side, cols=side, H=256)
-    announce("dag half steps groups %d N=%d" % (groups, wl.N))
+    announce("dag levels groups %d N=%d" % (groups, wl.N))
     C.cortex_set_knob(C.CORTEX_KNOB_FWD_SLICE_UNITS, 64)
     dw = run(wl, groups)
     assert C.cortex_last_grid(1) == 4 * groups
-    compare_states(dw.states_by_node(), O.forward_workload(wl), "dag half steps groups %d" % groups)
+    compare_states(dw.states_by_node(), O.forward_workload(wl), "dag levels groups %d" % groups)
 
 
 def test_dag_tile_list_overflow():
-    """One node group over 6 grids of 32x32: the group's steps (several per
-    level) exceed the per-workgroup step list many times over, so the kernel
+    """One node group over 6 grids of 32x32: the group's tiles (several per
+    level) exceed the per-workgroup list of 128 many times over, so the kernel
     lists and runs them a chunk at a time; against the oracle."""
     wl = I.dagrnn_workload(78, n_grids=6, rows=32, cols=32, H=256)
     announce("dag tile-list overflow N=%d" % wl.N)

@@ -125,7 +125,7 @@ def test_dag_64_grids_two_launches():
 def test_dag_large_batches(grids):
     """Batches beyond the headline's 64 grids of 32x32 through
     cortex_dag_infer: at 128 grids (131,072 nodes) each node group has about
-    95 steps, more than its step list holds, so it runs them in listed
+    128 tiles, the most its list holds, at 300 grids more, run in listed
     chunks; at 300 grids (307,200 nodes) the linearizer also takes its
     instance with two workgroups per compute unit.  Every state against the
     oracle."""

@@ -1,7 +1,9 @@
 """Kernels that contract split operands (three bf16 planes) on the bf16 matrix
 units: batch sizes on both sides of every rule that selects them, tiles with
-remainders, groups whose tile list runs in several chunks, operands and weights
-that cannot be split, and the accuracy of the sums themselves.  GPU."""
+remainders, groups whose tile list runs in several chunks, deep batches with few
+rows per level, operands and weights that cannot be split, and the accuracy of
+the sums themselves (tests/test_split_planes.py shows that the bound finds a lost
+or misplaced plane).  GPU."""
 import dataclasses
 
 import numpy as np
@@ -61,6 +63,7 @@ SIZES = {
     "mvrnn_d128_forest": lambda: I.mvrnn_workload(30, batch=23, d=128, leaf_lo=1, leaf_hi=50),
     "dag_h256_1x1": lambda: I.dagrnn_workload(10, n_grids=1, rows=1, cols=1, H=256),
     "dag_h256_6143": lambda: I.dagrnn_workload(25, n_grids=1, rows=1, cols=6143, H=256),
+    "dag_h256_29x31": lambda: I.dagrnn_workload(55, n_grids=7, rows=29, cols=31, H=256),
     "dag_h256_6144": lambda: I.dagrnn_workload(26, n_grids=2, rows=48, cols=64, H=256),
     "dag_h256_36863": lambda: I.dagrnn_workload(27, n_grids=191, rows=1, cols=193, H=256),
     "dag_h256_36865": lambda: I.dagrnn_workload(28, n_grids=365, rows=1, cols=101, H=256),
@@ -279,15 +282,27 @@ UNSPLITTABLE = {
     "nary": lambda: I.nary_treelstm_workload(20, batch=60, H=256, leaf_lo=20, leaf_hi=20),
     "childsum": lambda: childsum(24, 80, 20, 20),
     "tree_rnn": lambda: tree_rnn(21, 60, 30, 30, 256),
+    "tree_rnn_wide": lambda: tree_rnn(56, 104, 30, 30, 256),
+    "tree_rnn_h512": lambda: tree_rnn(57, 60, 30, 30, 512),
     "dag_h256": lambda: I.dagrnn_workload(22, n_grids=3, rows=5, cols=4, H=256),
+    "dag_h256_32": lambda: I.dagrnn_workload(58, n_grids=128, rows=7, cols=7, H=256),
+    "dag_h256_64": lambda: I.dagrnn_workload(59, n_grids=3, rows=5, cols=4, H=256),
     "dag_h512": lambda: I.dagrnn_workload(23, n_grids=2, rows=5, cols=4, H=512),
 }
+UNITS = {"dag_h256_64": 64}                  # slice width held by the knob
+
+
+@pytest.fixture
+def units(name):
+    C.cortex_set_knob(C.CORTEX_KNOB_FWD_SLICE_UNITS, UNITS.get(name, 0))
+    yield
+    C.cortex_set_knob(C.CORTEX_KNOB_FWD_SLICE_UNITS, 0)
 
 
 @pytest.mark.parametrize("value", [float("inf"), 3.4e38, -3.397e38, float("nan")])
 @pytest.mark.parametrize("where", ["input", "weight"])
 @pytest.mark.parametrize("name", sorted(UNSPLITTABLE))
-def test_unsplittable_values(name, where, value):
+def test_unsplittable_values(name, where, value, units):
     """One infinite, NaN or near-overflow input element or weight: the states
     are those of the definition (the gates saturate; NaN spreads to the same
     nodes and units)."""
@@ -313,6 +328,45 @@ def test_unsplittable_values(name, where, value):
         fine = np.isfinite(r32)
         assert np.array_equal(got[key][~fine & ~np.isnan(r32)], r32[~fine & ~np.isnan(r32)]), key
         assert float(np.abs(got[key][fine] - r32[fine]).max()) <= 1e-4 * max(1.0, float(np.abs(r32[fine]).max())), key
+
+
+ACCURACY = {
+    # name: (workload, slice-width knob), one for each kernel and slice width
+    "nary_8": (lambda: I.nary_treelstm_workload(62, batch=60, H=256), 0),
+    "nary_2": (lambda: I.nary_treelstm_workload(63, batch=60, H=256), 2),
+    "tree_rnn_16": (lambda: tree_rnn(64, 60, 30, 30, 256), 0),
+    "tree_rnn_64": (lambda: tree_rnn(65, 110, 30, 30, 256), 0),
+    "tree_rnn_h512_32": (lambda: tree_rnn(66, 60, 30, 30, 512), 0),
+    "dag_16_one_launch": (lambda: I.dagrnn_workload(67, n_grids=4, rows=9, cols=9, H=256), 0),
+    "dag_16": (lambda: I.dagrnn_workload(68, n_grids=30, rows=9, cols=9, H=256), 0),
+    "dag_32": (lambda: I.dagrnn_workload(69, n_grids=80, rows=9, cols=9, H=256), 0),
+    "dag_64": (lambda: I.dagrnn_workload(70, n_grids=10, rows=9, cols=9, H=256), 64),
+    "dag_h512": (lambda: I.dagrnn_workload(71, n_grids=30, rows=9, cols=9, H=512), 0),
+    "childsum": (lambda: childsum(72, 60, 20, 80), 0),
+    "mvrnn": (lambda: I.mvrnn_workload(73, batch=20, d=128), 0),
+    "mvrnn_one_launch": (lambda: I.mvrnn_workload(74, batch=1, d=128, leaf_lo=20, leaf_hi=20), 0),
+}
+
+
+@pytest.mark.parametrize("name", sorted(ACCURACY))
+def test_accuracy_of_the_sums(name):
+    """The computed states are off from 64 bits by at most 5e-7 of their
+    2-norm: fp32 rounding (0.9e-7 to 2.6e-7 with every plane product in place;
+    without any one of the six, 1e-6 or more)."""
+    make, units = ACCURACY[name]
+    wl = make()
+    announce("split accuracy %s N=%d" % (name, wl.N))
+    C.cortex_set_knob(C.CORTEX_KNOB_FWD_SLICE_UNITS, units)
+    try:
+        got = run(wl).states_by_node()
+    finally:
+        C.cortex_set_knob(C.CORTEX_KNOB_FWD_SLICE_UNITS, 0)
+    ref = O.forward_workload(wl)
+    inner = (wl.children.reshape(wl.N, wl.K) >= 0).any(1)        # (leaves copy their inputs)
+    for key in ref:
+        err = float(np.linalg.norm(got[key][inner] - ref[key][inner]) / np.linalg.norm(ref[key][inner]))
+        print("%s %s %.2g" % (name, key, err))
+        assert err <= 5e-7, key
 
 
 def test_mvrnn_tiny_matrices():
@@ -376,12 +430,14 @@ BEYOND = dict(
     # (one level: further up the huge weight would magnify the rounding of the states below)
     nary=lambda: I.nary_treelstm_workload(34, batch=520, H=256, leaf_lo=2, leaf_hi=2),
     tree_rnn=lambda: tree_rnn(35, 900, 2, 2, 256),
+    tree_rnn_wide=lambda: tree_rnn(60, 2049, 2, 2, 256),
+    tree_rnn_h512=lambda: tree_rnn(61, 860, 2, 2, 512),
 )
 
 
 @pytest.mark.parametrize("x,w", [(3e38, 2001.3), (-3e38, 2001.3), (2e30, 3e12), (1.0009e30, -3.003e12)])
 @pytest.mark.parametrize("name", sorted(BEYOND))
-def test_products_beyond_the_fp32_range(name, x, w):
+def test_products_beyond_the_fp32_range(name, x, w, units):
     """Finite inputs and weights, each of which can be split, whose product
     leaves the fp32 range: the sum is an infinity of that sign, as in fp32
     arithmetic (a gate saturates), and never NaN from two plane products that
