@@ -2418,35 +2418,36 @@ static void pick_slice(bool cached, Instance &out) {
 }
 
 template <int CELL, int H, int J>
-static bool pick_split(Instance &out, int32_t N, int32_t K, bool fused = false, bool cached = false) {
+static void pick_split(Instance &out, int32_t N, int32_t K, bool fused = false, bool cached = false) {
   using D = SplitDims<CELL, H, J>;
   constexpr bool kAblate = !(CELL == CELL_DAG && J > 16);       // has the instance without model persistence
   out.J = J;
   out.threads = kFwdThreads;
   out.level_barrier_ok = out.level_range_ok = true;
   out.ablate_bits = SrcCfg<CELL>::kLeafX ? 3 : 1;
-  if (D::kDag && kAblate && fused) {
-    out.fn = slice_split_kernel<CELL, H, J, D::kDag && kAblate>;
-    out.lds = split_list_bytes<D::CODES>(kSplitFusedCap) + (N + small_lin_ints<kFwdThreads>(N, 2)) * sizeof(int);
+  if constexpr (D::kDag && kAblate) {
+    if (fused) {
+      out.fn = slice_split_kernel<CELL, H, J, true>;
+      out.lds = split_list_bytes<D::CODES>(kSplitFusedCap) + small_lin_ints<kFwdThreads>(N, 2) * sizeof(int);
+      return;
+    }
+  }
+  out.lds = split_list_bytes<D::CODES>(kSplitCap);
+  const bool from_memory = knob(CORTEX_KNOB_ABLATE) & 1;
+  if constexpr (D::kDag || J < 8) {
+    out.fn = from_memory ? slice_split_kernel<CELL, H, J, false, kAblate> : slice_split_kernel<CELL, H, J, false>;
+  } else if (from_memory) {
+    out.fn = slice_split_kernel<CELL, H, J, false, kAblate>;
   } else {
-    out.lds = split_list_bytes<D::CODES>(kSplitCap);
-    const bool from_memory = knob(CORTEX_KNOB_ABLATE) & 1;
-    if constexpr (D::kDag || J < 8) {
-      out.fn = from_memory ? slice_split_kernel<CELL, H, J, false, kAblate> : slice_split_kernel<CELL, H, J, false>;
-    } else if (from_memory) {
-      out.fn = slice_split_kernel<CELL, H, J, false, kAblate>;
-    } else {
-      out.narrow_j = Cell<CELL, H>::J;
-      out.fn = slice_split_kernel<CELL, H, J, false, false, false, 1>;
-      if constexpr (CELL == CORTEX_NARY_TREELSTM) {
-        if (cached) {
-          out.fn = slice_split_kernel<CELL, H, J, false, false, false, 2>;
-          out.lds = std::max(out.lds, cache_ints(CELL, N, K) * sizeof(int));
-        }
+    out.narrow_j = Cell<CELL, H>::J;
+    out.fn = slice_split_kernel<CELL, H, J, false, false, false, 1>;
+    if constexpr (CELL == CORTEX_NARY_TREELSTM) {
+      if (cached) {
+        out.fn = slice_split_kernel<CELL, H, J, false, false, false, 2>;
+        out.lds = std::max(out.lds, cache_ints(CELL, N, K) * sizeof(int));
       }
     }
   }
-  return true;
 }
 
 // The split kernels of the slice cells at H = 256 and 512; false where there
@@ -2466,17 +2467,26 @@ static bool pick_split(Instance &out, int32_t N, int32_t K, bool fused = false, 
 //   DAG-RNN 256 (16)     100 nodes in one launch 69.8 / 64, 1,000 94 / 87
 //   DAG-RNN 512          1,000 179 / 147, 10,000 634 / 399 (J = 32: 220, 424)
 constexpr int kNarySplitMinRows = 1537, kTreeSplitMinRows = 2560, kTreeWideMinRows = 6144;
+static_assert((4 * (size_t)kTreeSplitMinRows + 1) * sizeof(int) > kStructCacheBudget,
+              "the split kernel checks every row of small batches of the N-ary TreeLSTM alone");
 static bool pick_slice_split(int cell, int H, int32_t N, int32_t K, int64_t units, bool fused, bool cached, Instance &out) {
   if (K != 2) return false;
-  if (cell == CORTEX_NARY_TREELSTM && H == 256 && !fused && N >= kNarySplitMinRows)
-    return units == 2 ? pick_split<CORTEX_NARY_TREELSTM, 256, 2>(out, N, K)
-                      : pick_split<CORTEX_NARY_TREELSTM, 256, 8>(out, N, K, false, cached);
-  if (cell == CORTEX_TREE_RNN && H == 256 && !fused && N >= kTreeSplitMinRows)
-    return N >= kTreeWideMinRows ? pick_split<CORTEX_TREE_RNN, 256, 64>(out, N, K) : pick_split<CORTEX_TREE_RNN, 256, 16>(out, N, K);
-  if (cell == CORTEX_TREE_RNN && H == 512 && !fused && N >= kTreeSplitMinRows) return pick_split<CORTEX_TREE_RNN, 512, 32>(out, N, K);
-  if (cell == CELL_DAG && H == 256) return pick_split<CELL_DAG, 256, 16>(out, N, K, fused);
-  if (cell == CELL_DAG && H == 512) return pick_split<CELL_DAG, 512, 16>(out, N, K, fused);
-  return false;
+  if (cell == CORTEX_NARY_TREELSTM && H == 256 && !fused && N >= kNarySplitMinRows) {
+    if (units == 2) pick_split<CORTEX_NARY_TREELSTM, 256, 2>(out, N, K);
+    else pick_split<CORTEX_NARY_TREELSTM, 256, 8>(out, N, K, false, cached);
+  } else if (cell == CORTEX_TREE_RNN && H == 256 && !fused && N >= kTreeSplitMinRows) {
+    if (N >= kTreeWideMinRows) pick_split<CORTEX_TREE_RNN, 256, 64>(out, N, K);
+    else pick_split<CORTEX_TREE_RNN, 256, 16>(out, N, K);
+  } else if (cell == CORTEX_TREE_RNN && H == 512 && !fused && N >= kTreeSplitMinRows) {
+    pick_split<CORTEX_TREE_RNN, 512, 32>(out, N, K);
+  } else if (cell == CELL_DAG && H == 256) {
+    pick_split<CELL_DAG, 256, 16>(out, N, K, fused);
+  } else if (cell == CELL_DAG && H == 512) {
+    pick_split<CELL_DAG, 512, 16>(out, N, K, fused);
+  } else {
+    return false;
+  }
+  return true;
 }
 
 // Child-sum TreeLSTM at H = 256: the split kernel from this size on, in two
@@ -2636,7 +2646,7 @@ static bool pick_fused(int cell, int H, int32_t N, int32_t K, Instance &out) {
     return true;
   }
   if (cell == CELL_DAG && (H == 256 || H == 512)) {
-    // (at H = 256 the batches below the 64-unit kernel's range)
+    // (at H = 256 the batches below those of 32- and 64-unit slices)
     if ((units != 0 && units != 16) || (H == 256 && units == 0 && N >= kDagWideMinRows)) return false;
     return pick_slice_split(cell, H, N, K, units, true, false, out);
   }

@@ -299,8 +299,8 @@ struct SplitDims {
   static_assert(PARTS <= 8 && H % J == 0 && J <= 64, "epilogue mapping");
 };
 
-// Bytes of dynamic LDS: the list; fused launches add the input row by node id
-// and the linearizer's arrays.
+// Bytes of dynamic LDS: the list; fused launches (DAG-RNN) add the linearizer's
+// arrays.
 template <int CODES>
 constexpr size_t split_list_bytes(int cap) { return (size_t)cap * TileList<CODES>::kInts * sizeof(int); }
 constexpr int kSplitCap = 128, kSplitFusedCap = 48;
@@ -407,7 +407,6 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
   // ---- structure: the group's tiles and their operand sources ----
   int bad = 0, total = 0, listed = 0;
   SmallLin m;
-  int *xnode = dyn + kCap * INTS;               // fused: the input row by node id
   auto row_of_slot = [&](int idx) __attribute__((always_inline)) -> int {
     const int *t = &list[(idx / kTileM) * INTS];
     const int row = t[0] + idx % kTileM;
@@ -419,15 +418,11 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
       const int row = row_of_slot(idx);
       int *cd = &list[(idx / kTileM) * INTS + HEAD + (idx % kTileM) * CODES];
       const int v = row >= 0 ? m.order[row] : -1;
-      if (kDag) cd[0] = v >= 0 ? -2 - v : -1;
+      cd[0] = v >= 0 ? -2 - v : -1;
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
-        int c = (v >= 0 && s < K) ? m.ch[v * K + s] : -1;
-        if (c >= 0) {
-          const int cr = m.nrow[c];
-          c = (kLeafInputs && !(a.ablate & 2) && cr < off1) ? (xnode[c] >= 0 ? -2 - xnode[c] : -1) : cr;
-        }
-        cd[kDag ? s + 1 : s] = c;
+        const int c = (v >= 0 && s < K) ? m.ch[v * K + s] : -1;
+        cd[s + 1] = c >= 0 ? m.nrow[c] : -1;
       }
     }
   };
@@ -489,8 +484,7 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
     }
   };
 
-  // (fused: the weight loads and the input rows share the round trip of the
-  // linearizer's children)
+  // (fused: the weight loads share the round trip of the linearizer's children)
   float4 wv[WS][NT][2];
   if constexpr (!kWeightsFromMemory) {
 #pragma unroll
@@ -501,34 +495,13 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
         for (int hf = 0; hf < 2; ++hf) wv[s][nt][hf] = wfrag(s, nt, hf, i16);
   }
   if constexpr (kFused) {
-    static_assert(!kWeightsFromMemory, "the ablation has no fused launch");
-    int xi[kFusedPer];
-#pragma unroll
-    for (int k = 0; k < kFusedPer; ++k) {
-      const int v = tid + k * kFwdThreads;
-      xi[k] = (kLeafInputs && v < N) ? a.x_index[v] : -1;
-    }
-    L = small_linearize<kFwdThreads, kFusedPer>(a.children, N, K, a.status, xnode + N, m, fused_lin_stamps(a));
+    static_assert(kDag && !kWeightsFromMemory, "the DAG-RNN without ablations");
+    L = small_linearize<kFwdThreads, kFusedPer>(a.children, N, K, a.status, dyn + kCap * INTS, m, fused_lin_stamps(a));
     if (L == 0) return;
     if (blockIdx.x == 0)
       small_lin_emit<kFwdThreads>(m, N, K, L, a.o_num_levels, a.o_height, a.o_level_offsets, a.o_level_nodes, a.o_node_row,
                                   a.o_child_rows);
     CORTEX_TRACE_KERNEL(9);
-    if constexpr (kLeafInputs) {
-#pragma unroll
-      for (int k = 0; k < kFusedPer; ++k) {
-        const int v = tid + k * kFwdThreads;
-        if (v < N) {
-          int x = xi[k];
-          if (x < -1 || x >= a.x_rows) {
-            raise_status(a.status, CORTEX_ST_INPUT_RANGE);
-            x = -1;
-          }
-          xnode[v] = x;
-        }
-      }
-    }
-    off1 = L > 1 ? m.lcount[1] : N;
     CORTEX_TRACE_KERNEL(10);
     if (status0 != 0) return;
   } else {
@@ -682,20 +655,10 @@ __global__ void __launch_bounds__(kFwdThreads) slice_split_kernel(FwdArgs a) {
       if (XS > 0) issue_x(code(list, i16, 0));
       issue_cells(list, 0);
     }
-    if (kLeafInputs && first == 0 && a.level_lo == 0) {
+    if constexpr (kLeafInputs) {
       // the leaf level: h = input row, c = 0 (its loads and stores overlap the
       // first tile's requests; no tile waits for these rows)
-      if constexpr (kFused) {
-        constexpr int H4 = H / 4;
-        for (int e = blockIdx.x * kFwdThreads + tid; e < off1 * H4; e += gridDim.x * kFwdThreads) {
-          const int xr = xnode[m.order[e / H4]];
-          *(float4 *)&a.h[(size_t)e * 4] =
-              as_float4(xin.load4(xr >= 0 ? (uint32_t)(xr * H + 4 * (e % H4)) * 4u : kNoSource));
-          if (kLstm) *(float4 *)&a.c[(size_t)e * 4] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-      } else {
-        write_leaf_outputs<H, kLstm>(a, nullptr, off1, hs, cs, tag);
-      }
+      if (first == 0 && a.level_lo == 0) write_leaf_outputs<H, kLstm>(a, nullptr, off1, hs, cs, tag);
     }
     // a tile's accumulators, and the largest operand met
     floatx4 hi[NT], lo[NT];
@@ -1350,10 +1313,8 @@ __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) 
           const float4 v1 = make_float4(as_float(flo[k][1].x), as_float(flo[k][1].z), as_float(fhi[k][1].x), as_float(fhi[k][1].z));
           // (an absent slot's loads read zeros)
           mx = max_abs(max_abs(mx, v0), v1);
-          if constexpr (HT > 0) {
-            h0 = make_float4(h0.x + v0.x, h0.y + v0.y, h0.z + v0.z, h0.w + v0.w);
-            h1 = make_float4(h1.x + v1.x, h1.y + v1.y, h1.z + v1.z, h1.w + v1.w);
-          }
+          h0 = make_float4(h0.x + v0.x, h0.y + v0.y, h0.z + v0.z, h0.w + v0.w);
+          h1 = make_float4(h1.x + v1.x, h1.y + v1.y, h1.z + v1.z, h1.w + v1.w);
           // the slot's next operands: the tile's next 32 columns, or the next tile's first
           const uint32_t so = s + 1 < RS ? child_off(cd[k]) + 256u * (s + 1) : child_off(cdn[k]);
           Split8 wl[1] = {wu[s][NT - 1]};
@@ -1362,11 +1323,9 @@ __global__ void __launch_bounds__(kFwdThreads) childsum_split_kernel(FwdArgs a) 
           });
           if constexpr (s == RS - 1) fh[k][0] += fl[k][0];
         });
-        if constexpr (HT > 0) {
-          mx = max_abs(max_abs(mx, h0), h1);
-          mfma_split<HT>(split8(h0, h1), reinterpret_cast<const Split8(&)[HT]>(wu[s]), reinterpret_cast<floatx4(&)[HT]>(hi),
-                         reinterpret_cast<floatx4(&)[HT]>(lo), [](auto) {});
-        }
+        mx = max_abs(max_abs(mx, h0), h1);
+        mfma_split<HT>(split8(h0, h1), reinterpret_cast<const Split8(&)[HT]>(wu[s]), reinterpret_cast<floatx4(&)[HT]>(hi),
+                       reinterpret_cast<floatx4(&)[HT]>(lo), [](auto) {});
       });
       if (mx >= limit) list[e * INTS + 3] = -1;           // read after the tile's barrier
       CORTEX_TRACE_WAVE(l);
