@@ -2060,10 +2060,11 @@ __device__ __forceinline__ bool level_bounds(const FwdArgs &a, int l, int &r0, i
 // exactly the child vectors and matrices it stages, and a leaf child is read
 // from the inputs (its state is the given (a, A)), so nothing waits on the
 // leaf level.  Child rows and the input rows of the leaves are cached in LDS
-// for batches of up to MvDims<D>::kCacheRows rows.
+// for batches of up to MvDims::kCacheRows rows.
 // ---------------------------------------------------------------------------
-template <int D>
+constexpr int kMvD = 64;
 struct MvDims {
+  static constexpr int D = kMvD;
   static constexpr int kThreads = 4 * D;                 // d/16 waves
   static constexpr int RB = D / 16;                      // row blocks of P per node
   static constexpr int kLd = 2 * D + 4;                  // W_M slice row stride
@@ -2074,21 +2075,19 @@ struct MvDims {
   static constexpr int kCacheRows = 3072;                // 3 ints per row beside the static LDS
   static_assert(kParts * 8 == 2 * D && kGroups * kThreads * 4 == 2 * D * D, "MV-RNN tiling");
 };
-constexpr int kMvD = 64;
 
 // Fused launches (cortex_tree_infer): the batch is linearized in LDS first.
 // Dynamic LDS (ints): child rows (2N), leaf input rows (N), level offsets
 // (N + 1), input row by node id (N), then the linearizer's arrays.
-template <int D>
-constexpr int kMvFusedPer = kFusedMaxNodes / MvDims<D>::kThreads;      // nodes per thread: N <= 2048
-template <int D>
+constexpr int kMvFusedPer = kFusedMaxNodes / MvDims::kThreads;      // nodes per thread: N <= 2048
 __host__ __device__ inline size_t mv_fused_ints(int N) {
-  return 5 * (size_t)N + 1 + small_lin_ints<MvDims<D>::kThreads>(N, 2);
+  return 5 * (size_t)N + 1 + small_lin_ints<MvDims::kThreads>(N, 2);
 }
 
-template <int D, bool kFused = false>
-__global__ void __launch_bounds__(MvDims<D>::kThreads) mvrnn_forward_kernel(FwdArgs a) {
-  using M = MvDims<D>;
+template <bool kFused = false>
+__global__ void __launch_bounds__(MvDims::kThreads) mvrnn_forward_kernel(FwdArgs a) {
+  using M = MvDims;
+  constexpr int D = M::D;
   constexpr int kThreads = M::kThreads, RB = M::RB, kLd = M::kLd, kAb = M::kAb, kGroups = M::kGroups;
   constexpr int kSide = M::kSide, kParts = M::kParts;
   constexpr int WPER = 16 * 2 * D / kThreads;
@@ -2137,7 +2136,7 @@ __global__ void __launch_bounds__(MvDims<D>::kThreads) mvrnn_forward_kernel(FwdA
   if constexpr (kFused) {
     // linearize the batch (its loads share the weights' round trip), then
     // child rows, level offsets and the leaves' input rows from LDS
-    constexpr int PER = kMvFusedPer<D>;
+    constexpr int PER = kMvFusedPer;
     int *xnode = lvo + N + 1, *lin = xnode + N;
     int xi[PER];
 #pragma unroll
@@ -2593,10 +2592,10 @@ static bool pick(int cell, int H, int32_t N, int32_t K, bool cached, Instance &o
     return true;
   }
   if (cell == CORTEX_MVRNN && H == kMvD) {
-    out.fn = mvrnn_forward_kernel<kMvD, false>;
-    out.J = MvDims<kMvD>::RB;
-    out.threads = MvDims<kMvD>::kThreads;
-    out.lds = N <= MvDims<kMvD>::kCacheRows ? 3 * (size_t)N * sizeof(int) : 0;
+    out.fn = mvrnn_forward_kernel<false>;
+    out.J = MvDims::RB;
+    out.threads = MvDims::kThreads;
+    out.lds = N <= MvDims::kCacheRows ? 3 * (size_t)N * sizeof(int) : 0;
     return true;
   }
   if (cell == CORTEX_MVRNN && H == MvCols::D) {
@@ -2651,10 +2650,10 @@ static bool pick_fused(int cell, int H, int32_t N, int32_t K, Instance &out) {
     return pick_slice_split(cell, H, N, K, units, true, false, out);
   }
   if (cell == CORTEX_MVRNN && H == kMvD && K == 2) {
-    out.fn = mvrnn_forward_kernel<kMvD, true>;
-    out.J = MvDims<kMvD>::RB;
-    out.threads = MvDims<kMvD>::kThreads;
-    out.lds = mv_fused_ints<kMvD>(N) * sizeof(int);
+    out.fn = mvrnn_forward_kernel<true>;
+    out.J = MvDims::RB;
+    out.threads = MvDims::kThreads;
+    out.lds = mv_fused_ints(N) * sizeof(int);
     return true;
   }
   if (cell == CORTEX_MVRNN && H == MvCols::D && K == 2 && N <= MvCols::kFusedRows) {

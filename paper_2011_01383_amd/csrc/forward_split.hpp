@@ -24,7 +24,8 @@
 // operands or the weights allow either (split_limit), every wave forms its partial
 // sums of the tile again on the fp32 matrix unit, operands and weights read from
 // memory (one infinite weight, every tile of one slice: 64 grids 402 -> 1,757 us,
-// 200 N-ary trees 188 -> 499, 200 child-sum trees 278 -> 576).  NaN needs no such path: it stays NaN in every plane.
+// 200 N-ary trees 188 -> 499, 200 child-sum trees 278 -> 576).  NaN needs no such
+// path: it stays NaN in every plane.
 #pragma once
 
 namespace cortex {
